@@ -1,0 +1,16 @@
+// Multiply kernels of 5-row stride-1 layers.
+#include "conv2d_multiply.hpp"
+
+namespace samd {
+
+int launch_multiply_rows5(const Conv2dGeom &g, int32_t *y, const void *ws, hipStream_t s, const int32_t *src) {
+    if (g.rh == 1 && g.two == 0) return launch_multiply_shape<1, 5, 0>(g, y, ws, s, src);
+    if (g.rh == 1 && g.two == 1) return launch_multiply_shape<1, 5, 1>(g, y, ws, s, src);
+    if (g.rh == 1 && g.two == 2) return launch_multiply_shape<1, 5, 2>(g, y, ws, s, src);
+    if (g.rh == 2 && g.two == 0) return launch_multiply_shape<2, 5, 0>(g, y, ws, s, src);
+    if (g.rh == 2 && g.two == 1) return launch_multiply_shape<2, 5, 1>(g, y, ws, s, src);
+    if (g.rh == 2 && g.two == 2) return launch_multiply_shape<2, 5, 2>(g, y, ws, s, src);
+    return kNoInstance;
+}
+
+}  // namespace samd

@@ -165,17 +165,19 @@ __global__ __launch_bounds__(kBlock) void relu_requant_stage_kernel(const int32_
     const int h = hp - g.ph;
     const bool inside = h >= 0 && h < g.H;
     const int32_t *src = acc + (nc * g.H + (inside ? h : 0)) * g.W;
+    const int32_t pad = conv2d_pad_value(g.xoff, g.layout_spaced);
     for (int q = threadIdx.x & ((1 << qshift) - 1); q < g.nq; q += 1 << qshift) {
         int32_t *dst = xs + row * g.ntw * g.nq + q;
         for (int t = 0; t < g.ntw; ++t) {
             const int delta = g.tw_tap0[t] + g.tw_ntaps[t] - g.Kmax;
             const int col0 = g.sw * (q * g.I + delta) + g.tw_phase[t] - g.pw;
             uint32_t word = 0;
-            if (inside)
+            if (inside || pad != 0)
                 for (int ii = 0; ii < g.I; ++ii) {
                     const int col = col0 + g.sw * ii;
-                    if (col >= 0 && col < g.W)
-                        word += (uint32_t)((int32_t)requant(src[col], shift, g.xbits) - g.xoff) << (ii * g.L);
+                    const int32_t v = inside && col >= 0 && col < g.W
+                                          ? (int32_t)requant(src[col], shift, g.xbits) - g.xoff : pad;
+                    word += (uint32_t)v << (ii * g.L);
                 }
             dst[t * g.nq] = (int32_t)word;
         }

@@ -11,6 +11,7 @@
 #include <cmath>
 #include <cstdio>
 #include <array>
+#include <cstdint>
 #include <limits>
 #include <functional>
 #include <map>
@@ -83,27 +84,109 @@ bool addressable(const samd_conv2d_desc &d, const Conv2dGeom &g) {
            (rows + rpb - 1) / rpb * 256 <= (int64_t)0xffffffff;
 }
 
-// Launch shape of one lane geometry: output rows per thread (rh), row groups per wave,
+// Batches between two reads of the lanes; returns how often a wave reads them.
+int64_t set_period(Conv2dGeom &t) {
+    const int64_t hold = (int64_t)t.G * t.nrt;           // steps the lanes hold
+    if (t.rows_path) {
+        t.period = (int32_t)std::min<int64_t>((int64_t)t.G * t.ntw, INT32_MAX);
+        if (t.KH == 3 && t.period > 1) t.period &= ~1;   // the multiply loop takes pairs of batches
+        return ((int64_t)t.cpw * t.ntw + t.period - 1) / t.period;
+    }
+    t.period = (int32_t)(hold >= kStepBatch ? std::min<int64_t>(hold / kStepBatch, INT32_MAX) : -hold);
+    if (t.period > 1) t.period &= ~1;                    // the multiply loop takes pairs of batches
+    const int64_t per = hold >= kStepBatch ? (int64_t)t.period * kStepBatch : hold;
+    return ((int64_t)t.cpw * t.nrt + per - 1) / per;
+}
+
+// The form of two-level lanes a launch can use (Conv2dGeom::two: the wave's lanes widened
+// in registers after every period and decoded into the tile once, instead of decoded after
+// every period), 0 for none.  Exact when every sum stays within its field: fewer than 2^L
+// periods for the 2 L-bit fields, the top lane's total over the slice within the bits above
+// it (1), or apart in 32 bits where an odd lane count leaves it above every widened field
+// (2).  odd_mask: the odd lanes of an accumulator shifted right by one lane.
+int wide_form(const Conv2dGeom &t, int64_t periods, i128 top_per_channel, uint64_t &odd_mask) {
+    const int L = t.L, nl = t.nl, top = (nl - 1) * L;
+    if (periods < 2 || nl < 2 || t.rh > 2 || t.wm * t.ks * 64 > kMaxWideThreads) return 0;
+    if (L < 30 && periods >= ((int64_t)1 << L)) return 0;
+    const i128 total = top_per_channel * t.cpw + 1;
+    int form = 1;
+    if (nl % 2) {
+        if (total * pow2(top) > pow2(63)) form = 2;
+    } else {
+        const int last = (nl - 2) * L;                   // the top lane in `odd`, the highest even lane in `even`
+        if (total * pow2(last) > pow2(63) || (i128)periods * pow2(L) > pow2(64 - last)) return 0;
+    }
+    odd_mask = 0;
+    for (int j = 1; j < nl - 1; j += 2) odd_mask |= (((uint64_t)1 << L) - 1) << ((j - 1) * L);
+    if (nl % 2 == 0) odd_mask |= ~(uint64_t)0 << ((nl - 2) * L);
+    return form;
+}
+
+// Modelled time of one launch of the multiply kernel, in units of 4 clocks.  The form
+// follows the kernel - a wave's instructions (multiply-adds, lane reads, write-out rows,
+// per-batch and fixed scalar work), the issue rate of the waves a SIMD holds, the texture
+// path's operand loads and the LDS atomics a compute unit's SIMDs share, a wave's own time
+// as the lower bound, whole items per compute unit - and its constants were fitted to 4480
+// launches of 113 layers timed on MI355X (mean error 17 %; the model's choice among the
+// timed launches of a layer is 5 % from the fastest on average).
+double multiply_cost(const Conv2dGeom &t, int64_t periods) {
+    const double waves = (double)t.wm * t.ks, acc = (double)kWaveM * t.rh;
+    const double mads = acc * t.cpw * t.nrt;
+    double reads, atomics = acc * t.nl;
+    if (t.two) {
+        reads = 1.05 * acc * periods * (t.two == 2 ? 8.0 : 6.0) + 1.07 * acc * (5.0 + 3.0 * t.nl);
+    } else {
+        reads = 1.07 * acc * periods * (4.0 + 2.0 * t.nl);
+        atomics *= periods;
+    }
+    const double cols = std::ceil((t.ncs > 1 ? t.cw : t.Wo) / 64.0);
+    const double out_rows = std::ceil((double)t.mblk * t.rows_blk / waves) * cols;
+    const double loads = t.rows_path ? (double)t.cpw * t.ntw * (t.rh + t.KH - 1.0) : (double)t.cpw * t.nrt * t.rh;
+    const double batches = (double)t.cpw * t.nrt / 3.0;
+    // eight accumulators (rh == 1) leave a wave waiting for its own products
+    const double slots = (t.rh == 1 ? 0.89 : 0.78) * mads + reads + 48.0 * out_rows + 253.0 +
+                         2.0 * t.lds_words / 256.0 / waves + batches * (t.rows_path ? 2.2 : 13.5);
+    // waves per SIMD the kernel's registers allow (as compiled for gfx950)
+    const int regs = t.two ? (t.rh == 1 ? (t.rows_path ? 6 : 5) : (t.two == 1 && t.rows_path ? 4 : 3))
+                           : (t.rh == 1 ? 7 : t.rh == 2 ? 5 : 4);
+    const double res = std::max(1.0, std::min(std::floor(163840.0 / (t.lds_words * 4.0 + 64.0)),
+                                              std::floor(4.0 * regs / waves)));
+    const double items = (double)t.tiles * t.nmb / 256.0;
+    const double held = std::min(res, std::max(1.0, std::ceil(items))) * waves / 4.0;   // waves per SIMD
+    const double clk = 4.0 * (1.0 + 0.89 / std::pow(held, 1.42));                       // clocks per instruction
+    const double share = std::max(items, 1.0);
+    const double work = share * waves / 4.0 * slots * clk;
+    const double tex = share * waves * loads * 9.5;
+    double busy = std::max(work, tex) + 0.06 * std::min(work, tex) + 0.13 * share * waves * atomics;
+    if (items > 1.0 && items <= res)
+        busy *= 0.4 + 0.6 * std::ceil(items) / items;
+    else if (items > res)
+        busy *= 1.0 + 0.2 * (std::ceil(items / res) - items / res) * res / items;
+    // workgroups of fewer than 4 waves do not fill a compute unit's SIMDs evenly: after
+    // another kernel some SIMDs get one wave more than the rest (launches of 1792
+    // 2-wave workgroups took 66-68 us instead of 56)
+    if (waves < 4.0 && items > 1.0) busy *= 1.0 + 0.6 / held;
+    // the waves of a large workgroup end, and write their tile, together
+    busy *= waves > 8.0 ? 1.3 : waves > 4.0 ? 1.08 : 1.0;
+    const double solo = slots * 6.8 + 66.0 * (batches + 2.0);
+    return (std::max(busy, solo) + 0.37 * solo) / 4.0 + 1400.0;
+}
+
+// Launch shapes of one lane geometry: output rows per thread (rh), row groups per wave,
 // output-channel waves (wm) and channel-slice waves (ks) per workgroup, and whether the
-// lane's rows share operand loads (3-row, stride-1 kernels).  Every candidate is priced
-// in issue cycles of one compute unit (units of 4 clocks): its SIMDs' multiply-adds and
-// decodes, and its texture path's operand loads (about 12 clocks per wave-wide load on
-// MI355X, shared by the 4 SIMDs), whichever binds, divided by an issue efficiency that
-// grows with the waves resident per SIMD (latency hiding), plus the last item's drain and
-// the operand-spread pass.  Returns false when no tile fits the LDS.  With `all`, every
-// launch shape that fits is also appended to it, priced.
-bool place_launch(const samd_conv2d_desc &d, Conv2dGeom &c, std::vector<Conv2dGeom> *all, bool &range_limited) {
+// lane's rows share operand loads (3- and 5-row, stride-1 kernels); the cheapest is kept.
+// Returns false when no tile fits the LDS.  With `all`, every launch shape that fits is
+// also appended to it, priced.
+bool place_launch(const samd_conv2d_desc &d, Conv2dGeom &c, i128 top_per_channel, std::vector<Conv2dGeom> *all,
+                  bool &range_limited) {
     const int grp_max = 64 / c.nqs;
-    const bool rows_ok = d.KH == 3 && d.stride_h == 1 && (c.ntw == 1 || c.ntw == 2);
+    const bool rows_ok = d.stride_h == 1 && ((d.KH == 3 && (c.ntw == 1 || c.ntw == 2)) || d.KH == 5);
     bool found = false;
     Conv2dGeom best = c;
     best.cost = 1e300;
     for (int rows = 0; rows <= (rows_ok ? 1 : 0); ++rows) {
-    for (int rh = 1; rh <= (rows ? 4 : 2); ++rh) {
+    for (int rh = 1; rh <= (rows && d.KH == 3 ? 4 : 2); ++rh) {
         if (rh > 1 && c.Ho < rh) continue;
-        // waves per SIMD the kernel's registers allow (as compiled for gfx950), and at
-        // most kResidentWavesPerSimd
-        const int reg_waves = std::min(kResidentWavesPerSimd, rh <= 2 ? 7 : (rh == 3 ? 5 : 4));
         for (int gr = grp_max; gr >= 1; --gr) {
             for (int wm : {1, 2, 4}) {
                 // at most 8 channel slices: 16-wave workgroups measured 1.0-1.8x slower than
@@ -147,33 +230,21 @@ bool place_launch(const samd_conv2d_desc &d, Conv2dGeom &c, std::vector<Conv2dGe
                         continue;
                     }
 
-                    // wave-instructions and operand loads of one workgroup's item
-                    const double waves = (double)wm * ks;
-                    const double nflush = std::ceil((double)t.cpw / c.G);
-                    const double mads = waves * kWaveM * rh * t.cpw * c.nrt * 1.08;
-                    // fix-up: and, add, xor on 64 bits (6 operations), the xor left out with
-                    // a spacer MSB
-                    const double decode = waves * nflush * kWaveM * rh *
-                                          ((c.result_signed ? (c.spacer ? 3.0 : 5.0) : 0.0) + 1.0 + 2.0 * c.nl);
-                    const double fixed = waves * 150.0 + (double)t.lds_tile / 64.0 * 3.0;
-                    const double wg = mads + decode + fixed;
-                    const double loads = waves * t.cpw * (rows ? c.ntw * (rh + 2.0) : (double)c.nrt * rh);
-                    // one compute unit's share of the items (taken as workgroups free up)
-                    const double items = std::max(1.0, (double)t.tiles * t.nmb / 256.0);
-                    const double valu = items * wg / 4.0;
-                    const double tex = items * loads * 3.0;
-                    const double busy = std::max(valu, tex) + 0.25 * std::min(valu, tex);
-                    // residency: LDS and registers
-                    const double res = std::max(1.0, std::min(std::floor(163840.0 / (t.lds_words * 4.0)),
-                                                              std::floor(4.0 * reg_waves / waves)));
-                    const double occ = std::min(items, res) * waves / 4.0;
-                    const double eff = occ / (occ + 0.7);
-                    const double drain = 0.5 * wg / waves;
-                    const double spread = (double)t.spread_words * (6.0 * c.I + 4.0) / 64.0 / 1024.0;
-                    // measured on MI355X: slices of about 32 channels balance the per-wave
-                    // fixed costs against scalar-load latency hiding
-                    const double slice = 1.0 + 0.15 * std::fabs(std::log2(t.cpw / 32.0));
-                    t.cost = (busy / eff + drain) * slice + spread;
+                    // lanes read into the tile after every period, or widened in between:
+                    // whichever is cheaper
+                    const int64_t periods = set_period(t);
+                    t.bias = t.result_signed ? t.msb_mask : 0;
+                    t.two = 0;
+                    t.odd_mask = 0;
+                    t.cost = multiply_cost(t, periods);
+                    Conv2dGeom w = t;
+                    w.two = wide_form(t, periods, top_per_channel, w.odd_mask);
+                    if (w.two) {
+                        w.cost = multiply_cost(w, periods);
+                        if (w.cost < t.cost) t = w;
+                    }
+                    // the operand spread (the permanent-spacer layout has none)
+                    if (!t.layout_spaced) t.cost += (double)t.spread_words * (0.65 * c.I + 0.8) * 1e-6 * 587.5;
                     if (all) all->push_back(t);
                     if (t.cost < best.cost) {
                         best = t;
@@ -303,9 +374,9 @@ int search_lanes(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, int xoff, 
             c.Hp = d.H + 2 * d.pad_h;
             c.macs_per_mad = (double)I * d.KW / (double)c.ntw;
             // the multiply-adds alone, spread perfectly over every SIMD, bound the cost below
-            const double floor_cost = (double)d.N * c.Ho * c.ncs * c.nqs * d.M * d.C * c.nrt / 64.0 / 1024.0;
+            const double floor_cost = 0.78 * (double)d.N * c.Ho * c.ncs * c.nqs * d.M * d.C * c.nrt / 64.0 / 1024.0;
             if (!all && found && floor_cost >= best.cost) continue;
-            if (!place_launch(d, c, all, range_limited)) continue;
+            if (!place_launch(d, c, (i128)d.KH * nj[c.nl - 1] * prod, all, range_limited)) continue;
             if (c.cost < best.cost) {
                 best = c;
                 found = true;
@@ -353,10 +424,9 @@ int search_conv2d(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, int space
         const samd_fmt xs = {xf.bits, 1};
         const size_t first = all ? all->size() : 0;
         if (search_layout(d, xs, wf, 1 << (xf.bits - 1), spacer, alt, err2, all) == SAMD_OK) {
-            // the correction: four table lookups and a multiply-add per output, issued after
-            // the last barrier where nothing hides their latency (about 40 issue cycles per
-            // output in measurements on MI355X)
-            const double correction = (double)d.N * d.M * alt.Ho * alt.Wo * 40.0 / 64.0 / 1024.0;
+            // the correction: in the packed layout one addition per output; in the
+            // permanent-spacer layout four table lookups, issued where little hides them
+            const double correction = (double)d.N * d.M * alt.Ho * alt.Wo * (spacer ? 20.0 : 0.5) / 64.0 / 1024.0;
             alt.cost += correction;
             if (all)
                 for (size_t i = first; i < all->size(); ++i) (*all)[i].cost += correction;
@@ -483,7 +553,9 @@ void clear_tuned_conv2d(const samd_conv2d_desc *d, samd_fmt xf, samd_fmt wf) {
 size_t conv2d_kw_bytes(const Conv2dGeom &g) { return ((size_t)g.kw_words * 4 + 255) / 256 * 256; }
 
 size_t conv2d_pre_bytes(const Conv2dGeom &g) {
-    return g.xoff ? ((size_t)g.M * (g.KH + 1) * (g.KW + 1) * 4 + 255) / 256 * 256 : 0;
+    // one sum per output channel, or the prefix table of the permanent-spacer layout
+    const size_t per = g.layout_spaced ? (size_t)(g.KH + 1) * (g.KW + 1) : 1;
+    return g.xoff ? ((size_t)g.M * per * 4 + 255) / 256 * 256 : 0;
 }
 
 size_t conv2d_queue_offset(const Conv2dGeom &g) { return conv2d_kw_bytes(g) + conv2d_pre_bytes(g); }

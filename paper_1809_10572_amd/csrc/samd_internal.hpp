@@ -24,11 +24,11 @@ constexpr int kConv1dMaxLanes = 4;
 constexpr int kStepBatch = 3;      // kernel-word steps fetched per scalar-load batch
 constexpr int kStreamPad = 2 * kStepBatch;  // zero steps after each kernel-word stream
 constexpr int kMaxBlockWaves = 16; // waves per conv2d workgroup
+constexpr int kMaxWideThreads = 512; // threads of a conv2d workgroup with two-level lanes (its registers allow no more)
 constexpr int kMaxLdsBytes = 65536; // LDS per conv2d workgroup
 constexpr int kNumXcd = 8;          // accelerator complexes (each with its own L2); workgroup p runs on p % 8
 constexpr int kTicketStride = 256;  // bytes between the conv2d ticket counters (one per XCD)
 constexpr int kQueueBytes = kNumXcd * kTicketStride;
-constexpr int kResidentWavesPerSimd = 6;  // conv2d multiply kernel, as measured (register-limited)
 
 // Geometry of one SAMD 2-D convolution.  Every operand word is a signed 32-bit
 // integer A = sum_i v_i 2^(i L) holding I input values of one stride phase of one
@@ -53,11 +53,20 @@ struct Conv2dGeom {
                                     // as a spacer bit (values fit L - 1 bits), so the decode leaves out
                                     // the fix-up's final xor and reads L - 1-bit fields (Sec. 6.1)
     uint64_t msb_mask;              // sign bit of lanes 0 .. nl-2
+    int32_t two;                    // 0: lanes are decoded into the output tile after every period;
+                                    // 1, 2: two-level lanes, widened in registers after every period and
+                                    // decoded once (2: the top lane is summed apart)
+    int32_t period;                 // batches between decodes (rows_path: kernel words of a channel;
+                                    // else batches of kStepBatch steps, or -steps when the lanes hold
+                                    // fewer steps than a batch)
+    uint64_t bias;                  // where the accumulators of signed results start: half a lane's range in
+                                    // every lane below the top one; 0 for unsigned results
+    uint64_t odd_mask;              // two != 0: lanes 1, 3, ... of V >> L
     int32_t ntw;                    // kernel words (and operand-word variants) per (channel, kernel row)
     int32_t tw_phase[kMaxTapWords], tw_tap0[kMaxTapWords], tw_ntaps[kMaxTapWords];
     int32_t nrt;                    // steps per channel: KH * ntw
     // launch shape
-    int32_t rows_path;              // 1: 3-row stride-1 kernel whose output rows share operand loads
+    int32_t rows_path;              // 1: 3- or 5-row stride-1 kernel whose output rows share operand loads
                                     // (kernel-word streams kernel-word-major within a channel)
     int32_t rh;                     // output rows per thread
     int32_t groups;                 // row groups per wave: 64 / nqs
@@ -86,6 +95,11 @@ struct Conv2dGeom {
     int32_t ncs;                    // column segments per output row
     int32_t qseg;                   // words between column segments: cw / I
 };
+
+// What the lanes hold outside the image.  Recentred activations: -xoff, the recentred
+// zero, so that every output takes all its taps and the correction is xoff times one sum of
+// weights per output channel; the permanent-spacer layout is defined with 0 there.
+inline constexpr int32_t conv2d_pad_value(int32_t xoff, int32_t layout_spaced) { return layout_spaced ? 0 : -xoff; }
 
 // 1-D convolution geometry (unsigned operands, 32x32 -> 64-bit products).
 struct Conv1dGeom {

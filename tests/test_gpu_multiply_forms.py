@@ -1,0 +1,114 @@
+"""Every form of the multiply kernel - rows shared by 3- and 5-row kernels, the general
+path, lanes decoded every period or widened in registers (two-level lanes, with the top
+lane inside its word and apart), column segments - against the oracle, bit-exact, at
+shapes where each begins or ends: odd channel counts and slices, periods of one batch, rows
+past the image, filters past M, and operands that drive every lane to its bound."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1809_10572_amd as samd
+import samd_workloads as wl
+from oracle import reference as ref
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+# (shape, x bits, x signed, w bits): 13-bit lanes of 4-bit operands hold 7 channels (both
+# layouts of the top lane), 9-bit lanes of 2-bit operands 7 or 4, 22-bit lanes of 8-bit 10;
+# 1x1 and strided kernels take the general path; 300 columns take column segments
+CASES = [
+    ((1, 41, 7, 19, 9, 3, 3, 1, 1, 1, 1), 4, False, 4),
+    ((2, 40, 6, 11, 17, 3, 3, 1, 1, 1, 1), 2, True, 2),
+    ((1, 37, 5, 13, 8, 3, 3, 1, 1, 1, 1), 8, True, 8),
+    ((1, 33, 4, 9, 8, 3, 3, 1, 1, 0, 1), 5, False, 5),
+    ((1, 23, 9, 14, 10, 5, 5, 1, 1, 2, 2), 4, False, 4),
+    ((1, 19, 6, 10, 8, 5, 3, 1, 1, 2, 1), 8, False, 8),
+    ((1, 66, 3, 17, 9, 1, 1, 1, 1, 0, 0), 4, True, 4),
+    ((1, 21, 11, 12, 8, 3, 3, 2, 2, 1, 1), 6, True, 4),
+    ((1, 9, 13, 23, 8, 11, 11, 4, 4, 2, 2), 4, False, 4),
+    ((1, 30, 3, 300, 8, 3, 3, 1, 1, 1, 1), 4, False, 4),
+    ((1, 20, 4, 9, 8, 3, 3, 1, 1, 1, 1), 3, False, 3),
+]
+
+
+def _operands(kind, shape, xb, xs, wb):
+    N, C, H, W, M, KH, KW = shape[:7]
+    xlo, xhi = wl.value_range(xb, xs)
+    wlo, whi = wl.value_range(wb, True)
+    if kind == "mixed":
+        rng = np.random.default_rng(sum(shape) + xb)
+        return wl.half_extremes(rng, (N, C, H, W), xb, xs), wl.half_extremes(rng, (M, C, KH, KW), wb, True)
+    x = xlo if kind == "low" else xhi       # every product at one extreme
+    return np.full((N, C, H, W), x), np.full((M, C, KH, KW), wlo if kind != "high" else whi)
+
+
+def _variants(cands):
+    """The candidates, and their lane geometries under launch shapes the list leaves out:
+    several rows per lane, one or more channel slices, shared rows or not."""
+    keys = [samd.plan_key(p) for p in cands]
+    seen = set()
+    for k in list(keys):
+        geometry = (k["lane_bits"], k["lanes"], k["x_offset"])
+        if geometry in seen or len(seen) >= 6:
+            continue
+        seen.add(geometry)
+        keys += [dict(k, shared_rows=shared, rows_per_thread=rows, rows_per_block=rows * groups, mblock=m, split_waves=ks)
+                 for shared in (0, 1) for rows in (1, 2, 3, 4) for groups in (1, 2) for m, ks in ((8, 1), (16, 2), (8, 4))]
+    return keys
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+@pytest.mark.parametrize("kind", ["mixed", "low", "high", "opposite"])
+def test_every_candidate_matches_the_oracle(case, kind):
+    shape, xb, xs, wb = CASES[case]
+    x, w = _operands(kind, shape, xb, xs, wb)
+    xf, wf = samd.Fmt(xb, xs), samd.Fmt(wb, True)
+    want = ref.conv2d(x.astype(np.int32), w.astype(np.int32), shape)
+    dev = lambda a, s: torch.from_numpy(a.astype(np.int8 if s else np.uint8)).to(DEV)
+    xp, wp = samd.pack(dev(x, xs), xb, xs), samd.pack(dev(w, True), wb, True)
+    cands = samd.conv2d_candidates(shape, xf, wf, samd.MAX_CANDIDATES)
+    keys, ran = _variants(cands), 0
+    # the mixed operands go through every variant, the others through every fourth
+    try:
+        for p in keys if kind == "mixed" else keys[::4]:
+            try:
+                samd.conv2d_use_plan(shape, xf, wf, p)
+            except samd.SamdError:
+                continue            # a launch shape this layer does not have
+            ran += 1
+            y = samd.conv2d(xp, xf, wp, wf, shape)
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(y.cpu().numpy(), want, err_msg=str(p))
+    finally:
+        samd.conv2d_untune(shape, xf, wf)
+    assert ran >= len(cands) // 4
+
+
+def test_few_steps_per_decode_on_the_general_path():
+    # one-bit 1x1 layers list lane geometries that hold fewer products than one batch of
+    # three steps; every listed one of the narrowest lanes is run
+    shape, xf, wf = (1, 13, 3, 20, 8, 1, 1, 1, 1, 0, 0), samd.Fmt(1, False), samd.Fmt(1, True)
+    rng = np.random.default_rng(5)
+    x = wl.uniform(rng, (1, 13, 3, 20), 1, False)
+    w = wl.uniform(rng, (8, 13, 1, 1), 1, True)
+    want = ref.conv2d(x, w, shape)
+    xp = samd.pack(torch.from_numpy(x.astype(np.uint8)).to(DEV), 1, False)
+    wp = samd.pack(torch.from_numpy(w.astype(np.int8)).to(DEV), 1, True)
+    seen = set()
+    for bits in (3, 4, 5):
+        for lanes in range(2, 9):
+            for rows in (1, 2, 3):
+                for ks in (1, 2):
+                    key = dict(lane_bits=bits, lanes=lanes, x_offset=0, shared_rows=0, rows_per_thread=1,
+                               rows_per_block=rows, mblock=8, split_waves=ks, layout_spaced=0, spacer_msb=0)
+                    try:
+                        samd.conv2d_use_plan(shape, xf, wf, key)
+                    except samd.SamdError:
+                        continue
+                    seen.add(samd.conv2d_plan(shape, xf, wf).flush_channels)
+                    y = samd.conv2d(xp, xf, wp, wf, shape)
+                    torch.cuda.synchronize()
+                    samd.conv2d_untune(shape, xf, wf)
+                    np.testing.assert_array_equal(y.cpu().numpy(), want, err_msg=str(key))
+    assert min(seen) >= 1
