@@ -20,7 +20,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsamd.so")
 SOURCES = ["api.cpp", "plan.cpp", "pack.hip", "conv1d.hip", "conv2d_multiply_rows3.hip",
            "conv2d_multiply_rows3_wide.hip", "conv2d_multiply_rows5.hip", "conv2d_multiply_general.hip", "conv2d_samd.hip",
-           "conv2d_i8.hip", "epilogue.hip", "lanewise.hip", "peaks.hip", "noalloc.hip"]
+           "conv2d_spread.hip", "conv2d_i8.hip", "epilogue.hip", "lanewise.hip", "peaks.hip", "noalloc.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall", "-Wno-unused-function",

@@ -34,10 +34,6 @@ constexpr int RM = kWaveM;
 // vector lanes - across the multiply loop.  Divisions by launch constants are
 // multiplications: the item and lane set-up took about 550 instructions, 2 us of every
 // launch, when it divided.
-struct Division {   // n / d = (n * mul) >> shift for 0 <= n < 2^31
-    uint32_t mul, shift;
-};
-
 struct MultiplyArgs {
     // items and lanes
     const int32_t *xs, *kw;
@@ -110,7 +106,7 @@ __device__ __forceinline__ int32_t low_field(uint32_t w, int L) {
 // The output tile in LDS, by byte offset.
 typedef int32_t __attribute__((address_space(3))) *TilePtr;
 __device__ __forceinline__ void tile_add(uint32_t at, int j, int32_t v) {
-    __hip_atomic_fetch_add((TilePtr)(at + 4 * j), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_add((TilePtr)(size_t)(at + 4 * j), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // Decode of one accumulator (Sec. 6).  Signed results: the accumulator started at the sign
@@ -735,12 +731,6 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
         // the write-out (and the tile's re-zeroing) ends before the next item's decodes
         __syncthreads();
     }
-}
-
-inline Division division(uint32_t d) {
-    uint32_t s = 0;
-    while (((uint64_t)1 << s) < d) ++s;
-    return {(uint32_t)((((uint64_t)1 << (31 + s)) + d - 1) / d), 31 + s};
 }
 
 // x / d = (x * mul) >> 16 for the lanes and waves it is used on: exact while x d < 65536

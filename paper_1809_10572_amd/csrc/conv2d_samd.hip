@@ -1,23 +1,13 @@
 // SAMD 2-D convolution for gfx950: convolution by long multiplication (Sec. 5) with
 // signed sign-extension and the underflow fix-up (Sec. 6).
 //
-// Three kernels:
+// The weights' side and the launchers:
 //  * prep_weights_kernel: every kernel row -> its kernel words (taps reversed, sign-
 //    extended, L bits apart), laid out as one contiguous stream per group of kWaveM
 //    output channels, so a wave walks its kernel words with scalar loads;
-//  * spread_kernel: every packed input row -> operand words, I values of one stride
-//    phase L bits apart (temporary spacer bits), negative values sign-extended, so that
-//    each word is the int32 sum_i v_i 2^(i L); rows of the zero padding are written too;
-//  * conv2d_samd_kernel: a workgroup owns a tile of output rows of one image and wm*8
-//    output channels.  Every lane reads its operand words straight from the spread buffer
-//    with raw buffer loads (L1/L2-resident: each word is reused by the workgroup's channel
-//    waves and kernel rows), every wave holds its 8 kernel words of a step in SGPRs
-//    (scalar loads from its kernel-word stream) and adds the exact signed 32x32 -> 64-bit
-//    products into 64-bit accumulators (v_mad_i64_i32).  Every G channels the
-//    accumulators are decoded - fix-up, lane extraction - and added into an LDS tile of
-//    int32 outputs (the tile is the only LDS use), which also performs the overlap-add of
-//    neighbouring words' partial lanes and sums the channel-split waves; finished rows
-//    are stored from the tile.
+//  * filter_sum_kernel, prefix_kernel: the correction of recentred activations.
+// Operand words are written by conv2d_spread.hip and multiplied by the kernel of
+// conv2d_multiply.hpp.
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -111,82 +101,6 @@ __global__ __launch_bounds__(256) void prefix_kernel(const uint32_t *__restrict_
     }
 }
 
-// Operand words xs[n][c][hp][t][q] for padded rows hp in [0, H + 2 ph), of the
-// activations minus xoff (recentred unsigned activations).  A block of 256
-// threads covers 256 / QP padded rows (QP, a power of two of at most 256, about nq / 2.5
-// threads per row): thread (row, q) builds words q, q + QP, ... of every kernel-word
-// variant t of its row from the packed input row (L1-resident; rows of the zero padding
-// give zeros).
-template <int B, bool S>
-__global__ __launch_bounds__(256) void spread_kernel(const uint32_t *__restrict__ x, const Conv2dGeom g, int qshift,
-                                                     int32_t *__restrict__ xs) {
-    constexpr int P = 32 / B;
-    // 32-bit row indices: the planner keeps N * C * Hp below 2^31
-    const uint32_t row = blockIdx.x * (256u >> qshift) + (threadIdx.x >> qshift);   // (n*C + c)*Hp + hp
-    if (row >= (uint32_t)(g.N * g.C * g.Hp)) return;
-    const uint32_t nc = row / (uint32_t)g.Hp;
-    const int hp = (int)(row - nc * (uint32_t)g.Hp);
-    const int h = hp - g.ph;
-    const bool inside = h >= 0 && h < g.H;
-    const uint32_t *src = x + ((int64_t)nc * g.H + (inside ? h : 0)) * g.xrw;
-    const int32_t pad = conv2d_pad_value(g.xoff, g.layout_spaced);
-    // words q, q + 2^qshift, ... of the row (one pass unless the row has more than 256)
-    for (int q = threadIdx.x & ((1 << qshift) - 1); q < g.nq; q += 1 << qshift) {
-        int32_t *dst = xs + (int64_t)row * g.ntw * g.nq + q;
-        for (int t = 0; t < g.ntw; ++t) {
-            const int delta = g.tw_tap0[t] + g.tw_ntaps[t] - g.Kmax;
-            const int col0 = g.sw * (q * g.I + delta) + g.tw_phase[t] - g.pw;
-            uint32_t word = 0;
-            if (inside || pad != 0) {
-                for (int ii = 0; ii < g.I; ++ii) {
-                    const int col = col0 + g.sw * ii;
-                    int32_t v = pad;
-                    if (inside && col >= 0 && col < g.W) {
-                        const uint32_t f = (src[col / P] >> ((col % P) * B)) & ((1u << B) - 1);
-                        v = (S ? ((int32_t)(f << (32 - B)) >> (32 - B)) : (int32_t)f) - g.xoff;
-                    }
-                    word += (uint32_t)v << (ii * g.L);
-                }
-            }
-            dst[t * g.nq] = (int32_t)word;
-        }
-    }
-}
-
-// The same operand words built from unpacked 8-bit values (int8 when S, else uint8; N C H W
-// row-major) instead of packed rows: the permanent-spacer layout written straight from
-// the values a caller holds.  Each value enters as its low b bits (sign-extended when S).
-template <int B, bool S>
-__global__ __launch_bounds__(256) void spread_bytes_kernel(const uint8_t *__restrict__ x, const Conv2dGeom g,
-                                                           int qshift, int32_t *__restrict__ xs) {
-    const uint32_t row = blockIdx.x * (256u >> qshift) + (threadIdx.x >> qshift);   // (n*C + c)*Hp + hp
-    if (row >= (uint32_t)(g.N * g.C * g.Hp)) return;
-    const uint32_t nc = row / (uint32_t)g.Hp;
-    const int hp = (int)(row - nc * (uint32_t)g.Hp);
-    const int h = hp - g.ph;
-    const bool inside = h >= 0 && h < g.H;
-    const uint8_t *src = x + ((int64_t)nc * g.H + (inside ? h : 0)) * g.W;
-    for (int q = threadIdx.x & ((1 << qshift) - 1); q < g.nq; q += 1 << qshift) {
-        int32_t *dst = xs + (int64_t)row * g.ntw * g.nq + q;
-        for (int t = 0; t < g.ntw; ++t) {
-            const int delta = g.tw_tap0[t] + g.tw_ntaps[t] - g.Kmax;
-            const int col0 = g.sw * (q * g.I + delta) + g.tw_phase[t] - g.pw;
-            uint32_t word = 0;
-            if (inside) {
-                for (int ii = 0; ii < g.I; ++ii) {
-                    const int col = col0 + g.sw * ii;
-                    if (col >= 0 && col < g.W) {
-                        const uint32_t f = src[col] & ((1u << B) - 1);
-                        const int32_t v = (S ? ((int32_t)(f << (32 - B)) >> (32 - B)) : (int32_t)f) - g.xoff;
-                        word += (uint32_t)v << (ii * g.L);
-                    }
-                }
-            }
-            dst[t * g.nq] = (int32_t)word;
-        }
-    }
-}
-
 }  // namespace
 
 int launch_conv2d_prepare(const uint32_t *w, const Conv2dGeom &g, void *ws, hipStream_t s) {
@@ -218,56 +132,6 @@ int launch_conv2d_prepare(const uint32_t *w, const Conv2dGeom &g, void *ws, hipS
     SAMD_FOR_EACH_FMT(SAMD_PREFIX_CASE)
 #undef SAMD_PREFIX_CASE
     return check_launch("conv2d correction table");
-}
-
-int launch_conv2d_spread(const uint32_t *x, const Conv2dGeom &g, void *ws, hipStream_t s, int32_t *dst) {
-    int32_t *xs = dst ? dst : (int32_t *)((char *)ws + conv2d_xs_offset(g));
-    // 2^qshift threads per row, each building about 2.5 of its words (words q, q + 2^qshift,
-    // ...): one word per thread was 5-23 % slower at the mid-size layer
-    const int qshift = spread_qshift(g.nq);
-    const int64_t nrows = (int64_t)g.N * g.C * g.Hp;
-    const int rpb = 256 >> qshift;
-    const int64_t blocks = (nrows + rpb - 1) / rpb;   // one thread group per row, no grid-stride loop
-    // the planner refuses layers that would need 2^32 threads or more (addressable())
-    if (blocks * 256 > (int64_t)0xffffffff) {
-        set_error("conv2d operand spread: more than 2^32 threads in one launch");
-        return SAMD_EUNSUPPORTED;
-    }
-    const unsigned sgrid = (unsigned)blocks;
-    bool launched = false;
-#define SAMD_SPREAD_CASE(B, SG)                                                                            \
-    if (!launched && g.xbits == B && (bool)g.xsigned == SG) {                                              \
-        hipLaunchKernelGGL((spread_kernel<B, SG>), dim3(sgrid), dim3(256), 0, s, x, g, qshift, xs);        \
-        launched = true;                                                                                   \
-    }
-    SAMD_FOR_EACH_FMT(SAMD_SPREAD_CASE)
-#undef SAMD_SPREAD_CASE
-    return check_launch("conv2d operand spread");
-}
-
-int launch_conv2d_spread_bytes(const void *x, const Conv2dGeom &g, int32_t *dst, hipStream_t s) {
-    const int qshift = spread_qshift(g.nq);
-    const int64_t nrows = (int64_t)g.N * g.C * g.Hp;
-    const int rpb = 256 >> qshift;
-    const int64_t blocks = (nrows + rpb - 1) / rpb;
-    // the planner refuses layers that would need 2^32 threads or more (addressable())
-    if (blocks * 256 > (int64_t)0xffffffff) {
-        set_error("conv2d spaced pack: more than 2^32 threads in one launch");
-        return SAMD_EUNSUPPORTED;
-    }
-    // the stored values' format: signed when the activations are (recentred unsigned
-    // activations are stored unsigned and shifted by xoff inside the kernel)
-    const bool sgn = g.xsigned != 0;
-    bool launched = false;
-#define SAMD_SPREAD_BYTES_CASE(B, SG)                                                                    \
-    if (!launched && g.xbits == B && sgn == SG) {                                                        \
-        hipLaunchKernelGGL((spread_bytes_kernel<B, SG>), dim3((unsigned)blocks), dim3(256), 0, s,       \
-                           (const uint8_t *)x, g, qshift, dst);                                          \
-        launched = true;                                                                                 \
-    }
-    SAMD_FOR_EACH_FMT(SAMD_SPREAD_BYTES_CASE)
-#undef SAMD_SPREAD_BYTES_CASE
-    return check_launch("conv2d spaced pack");
 }
 
 int resident_workgroups(const void *kernel, int block, size_t shm, int &out) {

@@ -69,21 +69,6 @@ __global__ __launch_bounds__(kBlock) void mismatch_kernel(const int32_t *__restr
     if ((threadIdx.x & 63) == 0 && c != 0) atomicAdd(count, c);
 }
 
-// Requantisation shift for a layer maximum.
-__device__ inline int requant_shift(int32_t layer_max, int bits) {
-    const uint32_t mx = layer_max > 0 ? (uint32_t)layer_max : 0u;
-    const int len = 32 - __clz(mx);   // bit length, 0 for 0
-    return len > bits ? len - bits : 0;
-}
-
-__device__ inline uint32_t requant(int32_t v, int shift, int bits) {
-    const int64_t r = v > 0 ? v : 0;
-    const int64_t half = shift ? (int64_t)1 << (shift - 1) : 0;
-    const int64_t q = (r + half) >> shift;
-    const int64_t top = ((int64_t)1 << bits) - 1;
-    return (uint32_t)(q < top ? q : top);
-}
-
 // Rows of at most kPackVals values: a workgroup takes whole consecutive rows (their
 // values are one contiguous run of acc), reads them coalesced into LDS as requantised
 // bytes, then builds and stores one packed word per thread.  Longer rows: one thread
@@ -140,47 +125,6 @@ __global__ __launch_bounds__(kBlock) void relu_requant_pack_long_kernel(const in
         for (int i = 0; i < P; ++i)
             if (i < cnt) word |= requant(a[i], shift, B) << (i * B);
         dst[w] = word;
-    }
-}
-
-// ReLU + requantisation written straight into the next layer's operand words: the
-// activations never take the dense packed form between layers, they go from the int32
-// accumulators into lanes with spacer bits (the layout the next layer multiplies).
-// Word q of kernel-word variant t of padded row hp of channel c of image n holds, lane
-// ii, the requantised activation of column sw (q I + delta_t + ii) + phase_t - pw of row
-// hp - ph, minus the next layer's recentring offset; columns and rows outside the image
-// are 0.  The same words the next layer's operand spread builds from packed rows.
-// A block of 256 threads covers 256 / QP padded rows, as that spread does.
-__global__ __launch_bounds__(kBlock) void relu_requant_stage_kernel(const int32_t *__restrict__ acc,
-                                                                    const int32_t *__restrict__ dev_max,
-                                                                    const Conv2dGeom g, int qshift,
-                                                                    int32_t *__restrict__ xs,
-                                                                    int32_t *__restrict__ dev_shift) {
-    const int shift = requant_shift(*dev_max, g.xbits);
-    if (dev_shift && blockIdx.x == 0 && threadIdx.x == 0) *dev_shift = shift;
-    const int64_t row = (int64_t)blockIdx.x * (kBlock >> qshift) + (threadIdx.x >> qshift);   // (n*C + c)*Hp + hp
-    if (row >= (int64_t)g.N * g.C * g.Hp) return;
-    const int hp = (int)(row % g.Hp);
-    const int64_t nc = row / g.Hp;
-    const int h = hp - g.ph;
-    const bool inside = h >= 0 && h < g.H;
-    const int32_t *src = acc + (nc * g.H + (inside ? h : 0)) * g.W;
-    const int32_t pad = conv2d_pad_value(g.xoff, g.layout_spaced);
-    for (int q = threadIdx.x & ((1 << qshift) - 1); q < g.nq; q += 1 << qshift) {
-        int32_t *dst = xs + row * g.ntw * g.nq + q;
-        for (int t = 0; t < g.ntw; ++t) {
-            const int delta = g.tw_tap0[t] + g.tw_ntaps[t] - g.Kmax;
-            const int col0 = g.sw * (q * g.I + delta) + g.tw_phase[t] - g.pw;
-            uint32_t word = 0;
-            if (inside || pad != 0)
-                for (int ii = 0; ii < g.I; ++ii) {
-                    const int col = col0 + g.sw * ii;
-                    const int32_t v = inside && col >= 0 && col < g.W
-                                          ? (int32_t)requant(src[col], shift, g.xbits) - g.xoff : pad;
-                    word += (uint32_t)v << (ii * g.L);
-                }
-            dst[t * g.nq] = (int32_t)word;
-        }
     }
 }
 
@@ -288,23 +232,6 @@ int launch_relu_requant_pack(const int32_t *acc, int64_t rows, int64_t len, cons
     }
     set_error("relu_requant_pack: unsupported bits");
     return SAMD_EINVAL;
-}
-
-int launch_relu_requant_stage(const int32_t *acc, const int32_t *dev_max, const Conv2dGeom &g, void *ws,
-                              int32_t *dev_shift, hipStream_t s, int32_t *dst) {
-    int32_t *xs = dst ? dst : (int32_t *)((char *)ws + conv2d_xs_offset(g));
-    const int qshift = spread_qshift(g.nq);   // ~2.5 words per thread, as the spread
-    const int64_t nrows = (int64_t)g.N * g.C * g.Hp;
-    const int rpb = kBlock >> qshift;
-    const int64_t blocks = (nrows + rpb - 1) / rpb;   // one thread group per row, no grid-stride loop
-    // the planner refuses layers that would need 2^32 threads or more (addressable())
-    if (blocks * kBlock > (int64_t)0xffffffff) {
-        set_error("relu_requant_stage: more than 2^32 threads in one launch");
-        return SAMD_EUNSUPPORTED;
-    }
-    hipLaunchKernelGGL(relu_requant_stage_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, s, acc, dev_max, g, qshift,
-                       xs, dev_shift);
-    return check_launch("relu_requant_stage");
 }
 
 int launch_relu_requant_nhwc_u8(const int32_t *acc, int N, int C, int H, int W, const int32_t *dev_max, int bits,

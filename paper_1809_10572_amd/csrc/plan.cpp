@@ -244,7 +244,7 @@ bool place_launch(const samd_conv2d_desc &d, Conv2dGeom &c, i128 top_per_channel
                         if (w.cost < t.cost) t = w;
                     }
                     // the operand spread (the permanent-spacer layout has none)
-                    if (!t.layout_spaced) t.cost += (double)t.spread_words * (0.65 * c.I + 0.8) * 1e-6 * 587.5;
+                    if (!t.layout_spaced) t.cost += (double)t.spread_words * (0.3 * c.I + 0.9) * 1e-6 * 587.5;
                     if (all) all->push_back(t);
                     if (t.cost < best.cost) {
                         best = t;
