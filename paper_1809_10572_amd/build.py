@@ -19,7 +19,8 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsamd.so")
 SOURCES = ["api.cpp", "plan.cpp", "pack.hip", "conv1d.hip", "conv2d_multiply_rows3.hip",
-           "conv2d_multiply_rows3_wide.hip", "conv2d_multiply_rows5.hip", "conv2d_multiply_general.hip", "conv2d_samd.hip",
+           "conv2d_multiply_rows3_wide.hip", "conv2d_multiply_rows5.hip", "conv2d_multiply_general.hip",
+           "conv2d_multiply_batches.hip", "conv2d_samd.hip",
            "conv2d_spread.hip", "conv2d_i8.hip", "epilogue.hip", "lanewise.hip", "peaks.hip", "noalloc.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -22,6 +22,7 @@ constexpr int kNoInstance = 1;
 int launch_multiply_rows3(const Conv2dGeom &g, int32_t *y, const void *ws, hipStream_t s, const int32_t *src);
 int launch_multiply_rows3_wide(const Conv2dGeom &g, int32_t *y, const void *ws, hipStream_t s, const int32_t *src);
 int launch_multiply_rows5(const Conv2dGeom &g, int32_t *y, const void *ws, hipStream_t s, const int32_t *src);
+int launch_multiply_batches(const Conv2dGeom &g, int32_t *y, const void *ws, hipStream_t s, const int32_t *src);
 int launch_multiply_general(const Conv2dGeom &g, int32_t *y, const void *ws, hipStream_t s, const int32_t *src);
 
 namespace {
@@ -222,7 +223,8 @@ struct WideLanes<0> {};
 // rows need RH + KHT - 1 operand words per (channel, kernel word) instead of KHT RH.  Every
 // operand load costs the compute unit's texture path far more cycles than a multiply-add
 // costs a SIMD, and the four SIMDs share that path.  0: any other layer, one operand word
-// per (row, step).  SG: the result is signed (either operand signed), so lanes need the
+// per (row, step); 1: such a layer whose channels have a multiple of three steps (3-row
+// kernels at any stride), whose operand offsets take half of the scalar instructions.  SG: the result is signed (either operand signed), so lanes need the
 // fix-up and are sign-extended.  SEG: rows are split into column segments.
 //
 // The multiply loop: batches of kernel words in SGPRs (scalar loads, one pointer that only
@@ -540,8 +542,9 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
                 flush();
             }
         } else {
-            // any other layer: batches of three consecutive steps of the slice (they may
-            // straddle channels), one operand word per row and step
+            // any other layer: batches of three consecutive steps of the slice, one operand
+            // word per row and step; they may straddle channels unless a channel's steps
+            // are whole batches (KHT == 1)
             int lb[RH];   // byte offset of the lane's word in channel 0, step 0
 #pragma unroll
             for (int r = 0; r < RH; ++r) {
@@ -550,7 +553,8 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
             }
             int32_t kA[3 * RM], aA[3][RH], kB[3 * RM], aB[3][RH];
             // operand offsets step by step: nq words to the next step of a channel, then on
-            // to the next channel; steps past the slice stop at the spare channel
+            // to the next channel; the steps requested past the slice stop at the spare
+            // channel (fewer than three steps per channel could pass it)
             int rt = 0;
             const int nrt = a->nrt;
             const int sb_max = (a->C * ch_stride + (nrt - 1) * nq) * 4;
@@ -558,16 +562,29 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
             auto load = [&](int32_t(&k)[3 * RM], int32_t(&a)[3][RH]) __attribute__((always_inline)) {
 #pragma unroll
                 for (int j = 0; j < 3 * RM; ++j) k[j] = kp[j];
+                if constexpr (KHT == 1) {
 #pragma unroll
-                for (int j = 0; j < 3; ++j) {
+                    for (int j = 0; j < 3; ++j)
 #pragma unroll
-                    for (int r = 0; r < RH; ++r) a[j][r] = buffer_word(xrs, lb[r], sb);
-                    sb += nq * 4;
-                    if (++rt == nrt) {
+                        for (int r = 0; r < RH; ++r) a[j][r] = buffer_word(xrs, lb[r], sb + j * nq * 4);
+                    sb += 3 * nq * 4;
+                    rt += 3;
+                    if (rt == nrt) {
                         rt = 0;
                         sb += ch_skip;
                     }
-                    sb = min(sb, sb_max);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) {
+#pragma unroll
+                        for (int r = 0; r < RH; ++r) a[j][r] = buffer_word(xrs, lb[r], sb);
+                        sb += nq * 4;
+                        if (++rt == nrt) {
+                            rt = 0;
+                            sb += ch_skip;
+                        }
+                        sb = min(sb, sb_max);
+                    }
                 }
                 kp += 3 * RM;
             };

@@ -167,7 +167,7 @@ int resident_workgroups(const void *kernel, int block, size_t shm, int &out) {
 int launch_conv2d_multiply(const Conv2dGeom &g, int32_t *y, const void *ws, hipStream_t s, const int32_t *src) {
     int st = kNoInstance;
     if (!g.rows_path)
-        st = launch_multiply_general(g, y, ws, s, src);
+        st = g.nrt % kStepBatch == 0 ? launch_multiply_batches(g, y, ws, s, src) : launch_multiply_general(g, y, ws, s, src);
     else if (g.KH == 5)
         st = launch_multiply_rows5(g, y, ws, s, src);
     else if (g.two)

@@ -126,50 +126,59 @@ int wide_form(const Conv2dGeom &t, int64_t periods, i128 top_per_channel, uint64
 // follows the kernel - a wave's instructions (multiply-adds, lane reads, write-out rows,
 // per-batch and fixed scalar work), the issue rate of the waves a SIMD holds, the texture
 // path's operand loads and the LDS atomics a compute unit's SIMDs share, a wave's own time
-// as the lower bound, whole items per compute unit - and its constants were fitted to 4480
-// launches of 113 layers timed on MI355X (mean error 17 %; the model's choice among the
-// timed launches of a layer is 5 % from the fastest on average).
+// as the lower bound, whole workgroups per compute unit of the busiest XCD - and its constants were fitted to 7658
+// launches of about 330 layers timed on MI355X (error 13 %; the model's choice among the
+// timed launches of a layer is 3.5 % from the fastest on average).
 double multiply_cost(const Conv2dGeom &t, int64_t periods) {
     const double waves = (double)t.wm * t.ks, acc = (double)kWaveM * t.rh;
     const double mads = acc * t.cpw * t.nrt;
     double reads, atomics = acc * t.nl;
     if (t.two) {
-        reads = 1.05 * acc * periods * (t.two == 2 ? 8.0 : 6.0) + 1.07 * acc * (5.0 + 3.0 * t.nl);
+        reads = 1.28 * acc * periods * (t.two == 2 ? 8.0 : 6.0) + 1.2 * acc * (5.0 + 3.0 * t.nl);
     } else {
-        reads = 1.07 * acc * periods * (4.0 + 2.0 * t.nl);
+        reads = 1.2 * acc * periods * (4.0 + 2.0 * t.nl);
         atomics *= periods;
     }
     const double cols = std::ceil((t.ncs > 1 ? t.cw : t.Wo) / 64.0);
     const double out_rows = std::ceil((double)t.mblk * t.rows_blk / waves) * cols;
     const double loads = t.rows_path ? (double)t.cpw * t.ntw * (t.rh + t.KH - 1.0) : (double)t.cpw * t.nrt * t.rh;
     const double batches = (double)t.cpw * t.nrt / 3.0;
-    // eight accumulators (rh == 1) leave a wave waiting for its own products
-    const double slots = (t.rh == 1 ? 0.89 : 0.78) * mads + reads + 48.0 * out_rows + 253.0 +
-                         2.0 * t.lds_words / 256.0 / waves + batches * (t.rows_path ? 2.2 : 13.5);
+    const double slots = (t.rh == 1 ? 0.72 : 0.77) * mads + reads + 57.6 * out_rows + 220.0 +
+                         2.0 * t.lds_words / 256.0 / waves + batches * (t.rows_path ? 2.06 : 14.9);
     // waves per SIMD the kernel's registers allow (as compiled for gfx950)
     const int regs = t.two ? (t.rh == 1 ? (t.rows_path ? 6 : 5) : (t.two == 1 && t.rows_path ? 4 : 3))
-                           : (t.rh == 1 ? 7 : t.rh == 2 ? 5 : 4);
+                           : (t.rh == 1 ? 7 : t.rh == 2 && t.rows_path ? 5 : 4);
     const double res = std::max(1.0, std::min(std::floor(163840.0 / (t.lds_words * 4.0 + 64.0)),
                                               std::floor(4.0 * regs / waves)));
-    const double items = (double)t.tiles * t.nmb / 256.0;
+    // workgroups per compute unit of the XCD with the most tiles (32 compute units each)
+    const double items = (double)((t.tiles + kNumXcd - 1) / kNumXcd) * t.nmb / 32.0;
     const double held = std::min(res, std::max(1.0, std::ceil(items))) * waves / 4.0;   // waves per SIMD
-    const double clk = 4.0 * (1.0 + 0.89 / std::pow(held, 1.42));                       // clocks per instruction
+    const double clk = 4.0 * (1.0 + 0.366 / std::pow(held, 1.86));                      // clocks per instruction
     const double share = std::max(items, 1.0);
-    const double work = share * waves / 4.0 * slots * clk;
-    const double tex = share * waves * loads * 9.5;
-    double busy = std::max(work, tex) + 0.06 * std::min(work, tex) + 0.13 * share * waves * atomics;
-    if (items > 1.0 && items <= res)
-        busy *= 0.4 + 0.6 * std::ceil(items) / items;
-    else if (items > res)
-        busy *= 1.0 + 0.2 * (std::ceil(items / res) - items / res) * res / items;
+    // the busiest compute unit holds whole workgroups
+    const double whole = items > 1.0 && items <= res ? std::ceil(items) / items - 1.0 : 0.0;
+    const double work = share * waves / 4.0 * slots * clk * (1.0 + 0.72 * whole);
+    const double tex = share * waves * loads * (t.rows_path ? 5.6 : 6.5) * (1.0 + 1.64 * whole);
+    double busy = std::pow(std::pow(work, 1.565) + std::pow(tex, 1.565), 1.0 / 1.565) + 0.11 * share * waves * atomics;
+    if (items > res) busy *= 1.0 + 0.194 * (std::ceil(items / res) - items / res) * res / items;
+    // one row per lane: three loads feed 24 products of eight accumulators; with two kernel
+    // words per row the wave waits for both more than the above says
+    if (t.rows_path && t.rh == 1 && t.ntw == 2 && !t.two) busy *= 1.08;
+    // two-level lanes of two rows leave three or four waves per SIMD to hide those loads
+    if (t.rows_path && t.rh == 2 && t.ntw == 2 && t.two) busy *= 1.13;
+    // three and four rows per lane press on the registers
+    if (t.rh > 2) busy *= 1.1;
     // workgroups of fewer than 4 waves do not fill a compute unit's SIMDs evenly: after
     // another kernel some SIMDs get one wave more than the rest (launches of 1792
     // 2-wave workgroups took 66-68 us instead of 56)
-    if (waves < 4.0 && items > 1.0) busy *= 1.0 + 0.6 / held;
+    if (waves < 4.0 && items > 1.0 && items <= 2.0 * res) busy *= 1.0 + 0.6 / held;
     // the waves of a large workgroup end, and write their tile, together
     busy *= waves > 8.0 ? 1.3 : waves > 4.0 ? 1.08 : 1.0;
-    const double solo = slots * 6.8 + 66.0 * (batches + 2.0);
-    return (std::max(busy, solo) + 0.37 * solo) / 4.0 + 1400.0;
+    const double solo = slots * 6.0 + 66.0 * (batches + 2.0);
+    // rounds of equal workgroups where not all are resident
+    const double rounds = items > res ? std::ceil(items / res - 0.02) : 1.0;
+    const double group = std::max(solo, waves * loads * 9.5);
+    return (std::max(busy, group * rounds) + 0.325 * solo) / 4.0 + 1650.0;
 }
 
 // Launch shapes of one lane geometry: output rows per thread (rh), row groups per wave,
@@ -374,7 +383,7 @@ int search_lanes(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, int xoff, 
             c.Hp = d.H + 2 * d.pad_h;
             c.macs_per_mad = (double)I * d.KW / (double)c.ntw;
             // the multiply-adds alone, spread perfectly over every SIMD, bound the cost below
-            const double floor_cost = 0.78 * (double)d.N * c.Ho * c.ncs * c.nqs * d.M * d.C * c.nrt / 64.0 / 1024.0;
+            const double floor_cost = 0.72 * (double)d.N * c.Ho * c.ncs * c.nqs * d.M * d.C * c.nrt / 64.0 / 1024.0;
             if (!all && found && floor_cost >= best.cost) continue;
             if (!place_launch(d, c, (i128)d.KH * nj[c.nl - 1] * prod, all, range_limited)) continue;
             if (c.cost < best.cost) {
