@@ -144,7 +144,7 @@ double multiply_cost(const Conv2dGeom &t, int64_t periods) {
     const double loads = t.rows_path ? (double)t.cpw * t.ntw * (t.rh + t.KH - 1.0) : (double)t.cpw * t.nrt * t.rh;
     const double batches = (double)t.cpw * t.nrt / 3.0;
     const double slots = (t.rh == 1 ? 0.72 : 0.77) * mads + reads + 57.6 * out_rows + 220.0 +
-                         2.0 * t.lds_words / 256.0 / waves + batches * (t.rows_path ? 2.06 : 14.9);
+                         2.0 * t.lds_words / 256.0 / waves + batches * (t.rows_path ? 2.06 : t.nrt % 3 == 0 ? 9.0 : 14.9);
     // waves per SIMD the kernel's registers allow (as compiled for gfx950)
     const int regs = t.two ? (t.rh == 1 ? (t.rows_path ? 6 : 5) : (t.two == 1 && t.rows_path ? 4 : 3))
                            : (t.rh == 1 ? 7 : t.rh == 2 && t.rows_path ? 5 : 4);
@@ -172,9 +172,12 @@ double multiply_cost(const Conv2dGeom &t, int64_t periods) {
     // another kernel some SIMDs get one wave more than the rest (launches of 1792
     // 2-wave workgroups took 66-68 us instead of 56)
     if (waves < 4.0 && items > 1.0 && items <= 2.0 * res) busy *= 1.0 + 0.6 / held;
+    // nor do two or three 4-wave workgroups fall on every compute unit (371 x 57 x 197 -> 85,
+    // stride 2, 8 bits: 83 us with 4 waves, 66 with 8)
+    else if (waves == 4.0 && items > 1.0 && items <= 3.0) busy *= 1.06;
     // the waves of a large workgroup end, and write their tile, together
     busy *= waves > 8.0 ? 1.3 : waves > 4.0 ? 1.08 : 1.0;
-    const double solo = slots * 6.0 + 66.0 * (batches + 2.0);
+    const double solo = slots * 6.0 + (t.rows_path ? 66.0 : 110.0) * (batches + 2.0);
     // rounds of equal workgroups where not all are resident
     const double rounds = items > res ? std::ceil(items / res - 0.02) : 1.0;
     const double group = std::max(solo, waves * loads * 9.5);
