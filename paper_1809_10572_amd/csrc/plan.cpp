@@ -8,6 +8,7 @@
 // accumulated into it before the lanes are decoded, and the planner picks among the
 // exact geometries the one with the lowest modelled cost.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <array>
@@ -581,61 +582,79 @@ size_t conv2d_workspace_bytes(const Conv2dGeom &g) {
     return conv2d_xs_offset(g) + ((size_t)(g.spread_words + spare) * 4 + 255) / 256 * 256;
 }
 
+namespace {
+
+// The geometry of L-bit lanes and I values per operand word; false where no word holds a
+// tap, a lane overflows or a limit of the kernel is passed.
+bool conv1d_geometry(const Conv1dGeom &g, int xbits, int kbits, const int32_t *taps, int L, int I, Conv1dGeom &c) {
+    const i128 xmax = pow2(xbits) - 1, kmax_v = pow2(kbits) - 1;
+    const i128 u32max = pow2(32) - 1, u64max = pow2(64) - 1;
+    int kmax = 0;
+    for (int k = 1; k <= g.K; ++k)
+        if (word_fits(kbits, false, L, k, 0, u32max)) kmax = k;
+    if (kmax == 0) return false;
+    c = g;
+    c.L = L;
+    c.I = I;
+    int t0[kMaxTapWords], nt[kMaxTapWords];
+    if (!split_taps(g.K, kmax, t0, nt, c.ngroups)) return false;
+    // lanes: j <-> output q*I + j - (K - 1); group g's window starts at q*I - t0[g]
+    int nl = I + g.K - 1, top = -1;
+    if (nl > 64) return false;
+    int nj[64] = {0};
+    for (int j = 0; j < nl; ++j) {
+        for (int q = 0; q < c.ngroups; ++q) nj[j] += pairs_in_lane(j, I, nt[q]);
+        if (nj[j]) top = j;
+    }
+    i128 total = 0;
+    for (int j = 0; j <= top; ++j) {
+        const i128 dmax = (i128)nj[j] * xmax * kmax_v;
+        if (j < top && dmax > pow2(L) - 1) return false;
+        if (j * L > 63 && dmax > 0) return false;
+        total += dmax * pow2(j * L);
+    }
+    if (total > u64max) return false;
+    c.nl = top + 1;
+    for (int q = 0; q < c.ngroups; ++q) {
+        c.g_tap0[q] = t0[q];
+        c.g_ntaps[q] = nt[q];
+        c.g_delta[q] = -t0[q];
+        uint64_t word = 0;
+        for (int s = 0; s < nt[q]; ++s) word |= (uint64_t)(uint32_t)taps[t0[q] + s] << (s * L);
+        c.g_word[q] = (uint32_t)word;
+    }
+    c.extra = (g.K - 1 + I - 1) / I;
+    if (c.extra > kMaxConv1dExtra) return false;
+    c.nwords = (c.nout + I - 1) / I;
+    return true;
+}
+
+}  // namespace
+
+// The lanes depend on the widths and the number of taps alone, so the search over them (10 us
+// of a call whose kernel takes 4.6) runs once for each of the 8 x 8 x 16 combinations; the
+// entries are single words that any thread may write with the same value.
 int plan_conv1d(int64_t n, samd_fmt xf, const int32_t *taps, int32_t K, samd_fmt kf, Conv1dGeom &best,
                 std::string &err) {
+    static std::atomic<uint16_t> lanes[8][8][16];
     Conv1dGeom g = {};
     g.n = n;
     g.nout = n - K + 1;
     g.bits = xf.bits;
     g.K = K;
     g.xrw = (int32_t)row_words(n, xf.bits);
-    const i128 xmax = pow2(xf.bits) - 1, kmax_v = pow2(kf.bits) - 1;
-    const i128 u32max = pow2(32) - 1, u64max = pow2(64) - 1;
+    std::atomic<uint16_t> &known = lanes[xf.bits - 1][kf.bits - 1][K - 1];
+    if (const int li = known.load(std::memory_order_relaxed))
+        if (conv1d_geometry(g, xf.bits, kf.bits, taps, li >> 8, li & 255, best)) return SAMD_OK;
     double best_cost = 1e300;
     bool found = false;
     for (int L = 1; L <= 32; ++L) {
-        int kmax = 0;
-        for (int k = 1; k <= K; ++k)
-            if (word_fits(kf.bits, false, L, k, 0, u32max)) kmax = k;
-        if (kmax == 0) continue;
         int imax = 0;
         for (int i = 1; i <= 32; ++i)
-            if (word_fits(xf.bits, false, L, i, 0, u32max)) imax = i;
+            if (word_fits(xf.bits, false, L, i, 0, pow2(32) - 1)) imax = i;
         for (int I = 1; I <= std::min(imax, kConv1dMaxLanes); ++I) {
-            Conv1dGeom c = g;
-            c.L = L;
-            c.I = I;
-            int t0[kMaxTapWords], nt[kMaxTapWords];
-            if (!split_taps(K, kmax, t0, nt, c.ngroups)) continue;
-            // lanes: j <-> output q*I + j - (K - 1); group g's window starts at q*I - t0[g]
-            int nl = I + K - 1, top = -1;
-            if (nl > 64) continue;
-            int nj[64] = {0};
-            for (int j = 0; j < nl; ++j) {
-                for (int q = 0; q < c.ngroups; ++q) nj[j] += pairs_in_lane(j, I, nt[q]);
-                if (nj[j]) top = j;
-            }
-            bool ok = true;
-            i128 total = 0;
-            for (int j = 0; j <= top && ok; ++j) {
-                i128 dmax = (i128)nj[j] * xmax * kmax_v;
-                if (j < top && dmax > pow2(L) - 1) ok = false;
-                if (j * L > 63 && dmax > 0) ok = false;
-                if (ok) total += dmax * pow2(j * L);
-            }
-            if (!ok || total > u64max) continue;
-            c.nl = top + 1;
-            for (int q = 0; q < c.ngroups; ++q) {
-                c.g_tap0[q] = t0[q];
-                c.g_ntaps[q] = nt[q];
-                c.g_delta[q] = -t0[q];
-                uint64_t word = 0;
-                for (int s = 0; s < nt[q]; ++s) word |= (uint64_t)(uint32_t)taps[t0[q] + s] << (s * L);
-                c.g_word[q] = (uint32_t)word;
-            }
-            c.extra = (K - 1 + I - 1) / I;
-            if (c.extra > kMaxConv1dExtra) continue;
-            c.nwords = (c.nout + I - 1) / I;
+            Conv1dGeom c;
+            if (!conv1d_geometry(g, xf.bits, kf.bits, taps, L, I, c)) continue;
             double cost = (double)c.ngroups * (1 + c.extra) * (2.0 + 3.0 * I) / I + 3.0 * (I + K) * (1 + c.extra) / I;
             if (cost < best_cost) {
                 best_cost = cost;
@@ -648,6 +667,7 @@ int plan_conv1d(int64_t n, samd_fmt xf, const int32_t *taps, int32_t K, samd_fmt
         err = "no exact SAMD lane geometry for this 1-D convolution";
         return SAMD_EUNSUPPORTED;
     }
+    known.store((uint16_t)(best.L << 8 | best.I), std::memory_order_relaxed);
     return SAMD_OK;
 }
 
