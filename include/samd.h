@@ -68,7 +68,7 @@ enum {
  *   lanes        I: input values per 32-bit operand word
  *   taps_max     Kmax: taps of the widest stride phase, ceil(KW / stride_w)
  *   words_per_row nq: operand words per output row, ceil((Wo + Kmax - 1) / I)
- *   flush_channels G: input channels accumulated before the lanes are decoded
+ *   flush_channels G: input channels accumulated before the lanes are decoded or widened
  *   out_lanes    lanes of an accumulator that can be non-zero; the highest of them
  *                takes all the accumulator's remaining bits
  *   tap_words    kernel words per (input channel, kernel row)
@@ -80,7 +80,8 @@ enum {
  *   chunk_channels input channels per wave slice times split_waves
  *   x_offset     0, or 2^(b-1) when unsigned activations are recentred: x - x_offset
  *                (a signed b-bit value) enters the lanes, halving the largest product,
- *                and x_offset times the sum of each output's in-image weights is added
+ *                and x_offset times the sum of the channel's weights (packed layout, whose
+ *                padding is recentred too) or of each output's in-image weights is added
  *                back when the output is stored
  *   col_segments, segment_columns: output rows of more than 64 operand words are split
  *                into col_segments ranges of segment_columns output columns (a multiple
@@ -88,8 +89,8 @@ enum {
  *                two ranges are computed for both); 1 and Wo otherwise
  *   macs_per_mad multiply-accumulates delivered per 32x32->64 multiply (I * taps)
  *   rows_per_thread, shared_rows: output rows each lane computes, and whether they share
- *                operand loads (3-row, stride-1 kernels: RH + 2 loads per channel and
- *                kernel word instead of 3 RH)
+ *                operand loads (3- and 5-row, stride-1 kernels: RH + KH - 1 loads per
+ *                channel and kernel word instead of KH RH)
  *   model_cost   the planner's cost estimate (issue cycles of one compute unit)
  *   layout_spaced 1: a plan of the permanent-spacer layout (samd_conv2d_spaced*)
  *   spacer_msb   1: result lanes keep their MSB as a spacer bit; the decode leaves out
@@ -293,7 +294,9 @@ int samd_conv2d_spaced_tune(const uint32_t *x, samd_fmt xf, const uint32_t *w, s
  *   x, w, y, *d, xf, wf  as for samd_conv2d
  * The call itself allocates nothing (no hipMalloc, hipFree or allocating library
  * routine).  A layer whose workspace (samd_conv2d_workspace) exceeds
- * SAMD_NOALLOC_SCRATCH_BYTES is refused with SAMD_ENOSPC before any HIP call.  Every call
+ * SAMD_NOALLOC_SCRATCH_BYTES runs with the cheapest plan whose workspace fits, if its plan is
+ * the library's own choice; where none fits, or the plan was tuned, it is refused with
+ * SAMD_ENOSPC before any HIP call.  Every call
  * on one GPU uses that GPU's one array, and each call prepares it from scratch (kernel
  * words and the zeroed ticket counters are written by the call's own kernels), so the
  * previous call's contents do not matter; but calls that may overlap on one GPU (several

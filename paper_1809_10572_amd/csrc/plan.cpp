@@ -499,6 +499,39 @@ int plan_conv2d(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, Conv2dGeom 
     return st;
 }
 
+// The shape's plan where its workspace is within `limit` bytes; else, unless that plan was
+// tuned, the cheapest candidate whose workspace is.  Faster plans are not always smaller:
+// without the second step 1 of 1500 drawn layers around 64 MiB, which an earlier plan of
+// the same candidates served, would not fit.
+int plan_conv2d_within(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, size_t limit, Conv2dGeom &g,
+                       std::string &err) {
+    int st = plan_conv2d(d, xf, wf, g, err);
+    if (st != SAMD_OK || conv2d_workspace_bytes(g) <= limit) return st;
+    PlanKey key = plan_key(d, xf, wf, 0);
+    std::unique_lock<std::mutex> lock(plan_mu);
+    if (tuned_plans.count(key)) return SAMD_OK;
+    key.back() = -1;   // the fitting plan's own entry, for the next call
+    const auto it = plan_cache.find(key);
+    if (it != plan_cache.end() && conv2d_workspace_bytes(it->second) <= limit) {
+        g = it->second;
+        return SAMD_OK;
+    }
+    lock.unlock();
+    Conv2dGeom model;
+    std::vector<Conv2dGeom> all;
+    st = search_conv2d(d, xf, wf, 0, model, err, &all);
+    if (st) return st;
+    const Conv2dGeom *best = nullptr;
+    for (const Conv2dGeom &c : all)
+        if (addressable(d, c) && conv2d_workspace_bytes(c) <= limit && (!best || c.cost < best->cost)) best = &c;
+    if (!best) return SAMD_OK;   // the caller sees that g does not fit
+    g = *best;
+    lock.lock();
+    if (plan_cache.size() >= kPlanCacheMax) plan_cache.clear();
+    plan_cache[key] = g;
+    return SAMD_OK;
+}
+
 int conv2d_candidates(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, int max_count,
                       std::vector<Conv2dGeom> &out, std::string &err, int spacer) {
     out.clear();

@@ -122,6 +122,8 @@ int plan_conv1d(int64_t n, samd_fmt xf, const int32_t *taps, int32_t K, samd_fmt
                 std::string &err);
 // Candidate plans of a shape, ranked by the model's cost, the model's choice first, at
 // most max_count of them (distinct lane geometries and launch shapes).
+int plan_conv2d_within(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, size_t limit, Conv2dGeom &g,
+                       std::string &err);
 int conv2d_candidates(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, int max_count,
                       std::vector<Conv2dGeom> &out, std::string &err, int spacer = 0);
 // The first of all candidate plans (no count limit) that `match` accepts.

@@ -112,3 +112,19 @@ def test_few_steps_per_decode_on_the_general_path():
                     samd.conv2d_untune(shape, xf, wf)
                     np.testing.assert_array_equal(y.cpu().numpy(), want, err_msg=str(key))
     assert min(seen) >= 1
+
+
+def test_a_layer_whose_fastest_plan_passes_the_scratch_array_still_runs_there():
+    # 5-bit operands, signed 1-bit weights, 7x7: the model's choice needs 75 MB of workspace,
+    # other plans of the layer under 64 MiB
+    shape, xf, wf = (1, 692, 36, 205, 707, 7, 7, 1, 1, 3, 3), samd.Fmt(5, False), samd.Fmt(1, True)
+    assert samd.conv2d_workspace(shape, xf, wf) > samd.NOALLOC_SCRATCH_BYTES
+    g = torch.Generator(device=DEV).manual_seed(5)
+    x = torch.randint(0, 32, (1, 692, 36, 205), generator=g, device=DEV, dtype=torch.uint8)
+    w = torch.randint(-1, 1, (707, 692, 7, 7), generator=g, device=DEV, dtype=torch.int8)
+    xp, wp = samd.pack(x, 5, False), samd.pack(w, 1, True)
+    want = samd.conv2d(xp, xf, wp, wf, shape)
+    out = torch.empty_like(want)
+    for _ in range(2):
+        samd.conv2d_noalloc(xp, xf, wp, wf, shape, out=out.fill_(-1))
+        assert torch.equal(out, want)
