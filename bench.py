@@ -120,7 +120,7 @@ def kernel_source_sha():
     """Hash of the sources that decide what the SAMD conv kernel reads and writes."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("conv2d_samd.hip", "plan.cpp", "samd_internal.hpp"):
+    for f in ("conv2d_samd.hip", "conv2d_multiply.hpp", "conv2d_spread.hip", "plan.cpp", "samd_internal.hpp"):
         with open(os.path.join(HERE, "paper_1809_10572_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
