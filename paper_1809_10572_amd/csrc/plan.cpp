@@ -140,7 +140,8 @@ double multiply_cost(const Conv2dGeom &t, int64_t periods) {
         reads = 1.2 * acc * periods * (4.0 + 2.0 * t.nl);
         atomics *= periods;
     }
-    const double cols = std::ceil((t.ncs > 1 ? t.cw : t.Wo) / 64.0);
+    // rows of at most 32 outputs leave several at a time
+    const double cols = t.ncs > 1 || t.Wo > 32 ? std::ceil((t.ncs > 1 ? t.cw : t.Wo) / 64.0) : t.Wo > 16 ? 0.5 : t.Wo > 8 ? 0.25 : 0.125;
     const double out_rows = std::ceil((double)t.mblk * t.rows_blk / waves) * cols;
     const double loads = t.rows_path ? (double)t.cpw * t.ntw * (t.rh + t.KH - 1.0) : (double)t.cpw * t.nrt * t.rh;
     const double batches = (double)t.cpw * t.nrt / 3.0;

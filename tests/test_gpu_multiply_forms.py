@@ -128,3 +128,18 @@ def test_a_layer_whose_fastest_plan_passes_the_scratch_array_still_runs_there():
     for _ in range(2):
         samd.conv2d_noalloc(xp, xf, wp, wf, shape, out=out.fill_(-1))
         assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("width", [1, 7, 8, 9, 16, 17, 32, 33])
+@pytest.mark.parametrize("bits,signed", [(8, False), (3, True)])
+def test_rows_written_several_at_a_time(width, bits, signed):
+    # 8, 4 or 2 output rows leave a wave at once up to 8, 16 and 32 columns; 13 filters and 11
+    # rows leave tiles, channel blocks and lanes part empty; 8-bit plans are recentred
+    shape, xf, wf = (3, 6, 11, width, 13, 3, 3, 1, 1, 1, 1), samd.Fmt(bits, signed), samd.Fmt(bits, True)
+    x, w = _operands("mixed", shape, bits, signed, bits)
+    want = torch.from_numpy(np.asarray(ref.conv2d(x, w, shape))).to(DEV, torch.int32)
+    xt = torch.from_numpy(x.astype(np.int8 if signed else np.uint8)).to(DEV)
+    wp = samd.pack(torch.from_numpy(w.astype(np.int8)).to(DEV), bits, True)
+    assert torch.equal(samd.conv2d(samd.pack(xt, bits, signed), xf, wp, wf, shape), want)
+    ws = samd.conv2d_spaced_prepare(wp, wf, shape, xf)
+    assert torch.equal(samd.conv2d_spaced(samd.conv2d_spaced_pack(xt, xf, wf, shape), xf, wf, shape, ws), want)
