@@ -695,12 +695,14 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
         const int rows_blk = o->rows_blk, nwaves = o->waves, M = o->M, Ho = o->Ho, mblk = o->mblk, xoff = o->xoff;
         const int dmm = (nwaves * o->rows_mul) >> 16, dr = nwaves - dmm * rows_blk;
         constexpr int U = 4;
-        // Rows of at most 32 outputs: a wave copies 2, 4 or 8 rows at once, each lane working
-        // out its own.  A row of a wave of its own costs about 58 instructions whatever its
+        // Rows of at most 64 outputs: each lane works out its own row, and a wave copies 2, 4 or 8
+        // rows of at most 32, 16 or 8 outputs at once.  A row of a wave of its own costs about 58 instructions whatever its
         // length, which is most of the time of layers with few input channels: 13 x 5 x 219 x
-        // 32 -> 244, 3x3, 8 bits 113 -> 60 us, 10 x 3 x 182 x 23 -> 157 52 -> 23 us.
+        // 32 -> 244, 3x3, 8 bits 113 -> 60 us, 10 x 3 x 182 x 23 -> 157 52 -> 23 us; one row of
+        // 33 to 64 at a time is still shorter in vector than in scalar instructions: 2 x 16 x 34 x
+        // 34 -> 490, 1x1, 18.3 -> 16.1 us, 12 x 46 x 26 x 54 -> 214, 3x3, 33.0 -> 30.3.
         const int lane_rows = SEG || o->Wo > 32 ? 1 : o->Wo > 16 ? 2 : o->Wo > 8 ? 4 : 8;
-        if (lane_rows > 1) {
+        if (!SEG && o->Wo <= 64) {
             const int width = 64 / lane_rows, col = lane & (width - 1);
             const int step = nwaves * lane_rows, smm = (step * o->rows_mul) >> 16, sr = step - smm * rows_blk;
             const int row = wave * lane_rows + lane / width;
@@ -746,7 +748,7 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
                 }
             }
         }
-        int mm = lane_rows > 1 ? mblk : (wave * o->rows_mul) >> 16, r = wave - mm * rows_blk;
+        int mm = !SEG && o->Wo <= 64 ? mblk : (wave * o->rows_mul) >> 16, r = wave - mm * rows_blk;
         while (mm < mblk) {
             uint32_t src[U];
             int32_t *dst[U], add[U];
