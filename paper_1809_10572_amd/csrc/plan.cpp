@@ -130,7 +130,9 @@ int wide_form(const Conv2dGeom &t, int64_t periods, i128 top_per_channel, uint64
 // as the lower bound, whole workgroups per compute unit of the busiest XCD - and its constants were fitted to 7658
 // launches of about 330 layers timed on MI355X (error 13 %; the model's choice among the
 // timed launches of a layer is 3.5 % from the fastest on average).
-double multiply_cost(const Conv2dGeom &t, int64_t periods) {
+// A launch that is certain to cost `most` or more is priced no further: what is returned then is
+// a lower bound of at least `most`, from the terms that need no pow().
+double multiply_cost(const Conv2dGeom &t, int64_t periods, double most) {
     const double waves = (double)t.wm * t.ks, acc = (double)kWaveM * t.rh;
     const double mads = acc * t.cpw * t.nrt;
     double reads, atomics = acc * t.nl;
@@ -155,35 +157,41 @@ double multiply_cost(const Conv2dGeom &t, int64_t periods) {
     // workgroups per compute unit of the XCD with the most tiles (32 compute units each)
     const double items = (double)((t.tiles + kNumXcd - 1) / kNumXcd) * t.nmb / 32.0;
     const double held = std::min(res, std::max(1.0, std::ceil(items))) * waves / 4.0;   // waves per SIMD
-    const double clk = 4.0 * (1.0 + 0.366 / std::pow(held, 1.86));                      // clocks per instruction
     const double share = std::max(items, 1.0);
     // the busiest compute unit holds whole workgroups
     const double whole = items > 1.0 && items <= res ? std::ceil(items) / items - 1.0 : 0.0;
-    const double work = share * waves / 4.0 * slots * clk * (1.0 + 0.72 * whole);
     const double tex = share * waves * loads * (t.rows_path ? 5.6 : 6.5) * (1.0 + 1.64 * whole);
-    double busy = std::pow(std::pow(work, 1.565) + std::pow(tex, 1.565), 1.0 / 1.565) + 0.11 * share * waves * atomics;
-    if (items > res) busy *= 1.0 + 0.194 * (std::ceil(items / res) - items / res) * res / items;
-    // one row per lane: three loads feed 24 products of eight accumulators; with two kernel
-    // words per row the wave waits for both more than the above says
-    if (t.rows_path && t.rh == 1 && t.ntw == 2 && !t.two) busy *= 1.08;
-    // two-level lanes of two rows leave three or four waves per SIMD to hide those loads
-    if (t.rows_path && t.rh == 2 && t.ntw == 2 && t.two) busy *= 1.13;
-    // three and four rows per lane press on the registers
-    if (t.rh > 2) busy *= 1.1;
-    // workgroups of fewer than 4 waves do not fill a compute unit's SIMDs evenly: after
-    // another kernel some SIMDs get one wave more than the rest (launches of 1792
-    // 2-wave workgroups took 66-68 us instead of 56)
-    if (waves < 4.0 && items > 1.0 && items <= 2.0 * res) busy *= 1.0 + 0.6 / held;
-    // nor do two or three 4-wave workgroups fall on every compute unit (371 x 57 x 197 -> 85,
-    // stride 2, 8 bits: 83 us with 4 waves, 66 with 8)
-    else if (waves == 4.0 && items > 1.0 && items <= 3.0) busy *= 1.06;
-    // the waves of a large workgroup end, and write their tile, together
-    busy *= waves > 8.0 ? 1.3 : waves > 4.0 ? 1.08 : 1.0;
     const double solo = slots * 6.0 + (t.rows_path ? 66.0 : 110.0) * (batches + 2.0);
     // rounds of equal workgroups where not all are resident
     const double rounds = items > res ? std::ceil(items / res - 0.02) : 1.0;
     const double group = std::max(solo, waves * loads * 9.5);
-    return (std::max(busy, group * rounds) + 0.325 * solo) / 4.0 + 1650.0;
+    const auto total = [&](double busy) {
+        busy += 0.11 * share * waves * atomics;
+        if (items > res) busy *= 1.0 + 0.194 * (std::ceil(items / res) - items / res) * res / items;
+        // one row per lane: three loads feed 24 products of eight accumulators; with two kernel
+        // words per row the wave waits for both more than the above says
+        if (t.rows_path && t.rh == 1 && t.ntw == 2 && !t.two) busy *= 1.08;
+        // two-level lanes of two rows leave three or four waves per SIMD to hide those loads
+        if (t.rows_path && t.rh == 2 && t.ntw == 2 && t.two) busy *= 1.13;
+        // three and four rows per lane press on the registers
+        if (t.rh > 2) busy *= 1.1;
+        // workgroups of fewer than 4 waves do not fill a compute unit's SIMDs evenly: after
+        // another kernel some SIMDs get one wave more than the rest (launches of 1792
+        // 2-wave workgroups took 66-68 us instead of 56)
+        if (waves < 4.0 && items > 1.0 && items <= 2.0 * res) busy *= 1.0 + 0.6 / held;
+        // nor do two or three 4-wave workgroups fall on every compute unit (371 x 57 x 197 -> 85,
+        // stride 2, 8 bits: 83 us with 4 waves, 66 with 8)
+        else if (waves == 4.0 && items > 1.0 && items <= 3.0) busy *= 1.06;
+        // the waves of a large workgroup end, and write their tile, together
+        busy *= waves > 8.0 ? 1.3 : waves > 4.0 ? 1.08 : 1.0;
+        return (std::max(busy, group * rounds) + 0.325 * solo) / 4.0 + 1650.0;
+    };
+    // issue at a clock each 4 cycles, with nothing added for the texture path
+    const double least = total((1.0 - 1e-9) * std::max(share * waves * slots * (1.0 + 0.72 * whole), tex));
+    if (least >= most) return least;
+    const double clk = 4.0 * (1.0 + 0.366 / std::pow(held, 1.86));                      // clocks per instruction
+    const double work = share * waves / 4.0 * slots * clk * (1.0 + 0.72 * whole);
+    return total(std::pow(std::pow(work, 1.565) + std::pow(tex, 1.565), 1.0 / 1.565));
 }
 
 // Launch shapes of one lane geometry: output rows per thread (rh), row groups per wave,
@@ -191,54 +199,63 @@ double multiply_cost(const Conv2dGeom &t, int64_t periods) {
 // lane's rows share operand loads (3- and 5-row, stride-1 kernels); the cheapest is kept.
 // Returns false when no tile fits the LDS.  With `all`, every launch shape that fits is
 // also appended to it, priced.
-bool place_launch(const samd_conv2d_desc &d, Conv2dGeom &c, i128 top_per_channel, std::vector<Conv2dGeom> *all,
-                  bool &range_limited) {
+bool place_launch(const samd_conv2d_desc &d, Conv2dGeom &c, i128 top_per_channel, double most,
+                  std::vector<Conv2dGeom> *all, bool &range_limited) {
     const int grp_max = 64 / c.nqs;
     const bool rows_ok = d.stride_h == 1 && ((d.KH == 3 && (c.ntw == 1 || c.ntw == 2)) || d.KH == 5);
     bool found = false;
-    Conv2dGeom best = c;
-    best.cost = 1e300;
+    c.spread_words = (int64_t)d.N * d.C * c.Hp * c.ntw * c.nq;
+    // the operand spread (the permanent-spacer layout has none)
+    const double spread = c.layout_spaced ? 0.0 : (double)c.spread_words * (0.3 * c.I + 0.9) * 1e-6 * 587.5;
+    Conv2dGeom best = c, t = c;
+    best.cost = most;
     for (int rows = 0; rows <= (rows_ok ? 1 : 0); ++rows) {
     for (int rh = 1; rh <= (rows && d.KH == 3 ? 4 : 2); ++rh) {
         if (rh > 1 && c.Ho < rh) continue;
         for (int gr = grp_max; gr >= 1; --gr) {
+            const int rows_blk = std::min(rh * gr, c.Ho), row_tiles = (c.Ho + rows_blk - 1) / rows_blk;
+            const double xcd_tiles = (d.N * row_tiles * c.ncs + kNumXcd - 1) / kNumXcd;
+            // tile row stride: the columns a row needs, padded so that the rows of
+            // neighbouring lane groups start on different LDS banks (row groups are
+            // rh rows apart; their offset mod 32 banks should not be a multiple of
+            // the lane stride I)
+            int tile_row = c.nqs * c.I + c.Kmax - 1;
+            for (int pad = 0; pad < c.I && c.I > 1; ++pad)
+                if ((rh * (tile_row + pad)) % 32 % c.I != 0) {
+                    tile_row += pad;
+                    break;
+                }
             for (int wm : {1, 2, 4}) {
                 // at most 8 channel slices: 16-wave workgroups measured 1.0-1.8x slower than
                 // 8-wave ones on 512-channel layers (all 16 waves decode into one tile)
                 for (int ks : {1, 2, 4, 8}) {
                     if (wm * ks > kMaxBlockWaves) continue;
                     if (ks > 1 && (d.C + ks - 1) / ks < 1) continue;
-                    Conv2dGeom t = c;
+                    t.cpw = (d.C + ks - 1) / ks;           // channels per slice
+                    t.mblk = wm * kWaveM;
+                    t.nmb = (d.M + t.mblk - 1) / t.mblk;
+                    // most launch shapes are far from the cheapest: their multiply-adds alone
+                    // show it, without a look at the rest
+                    const double slots = (1.0 - 1e-9) * (0.72 * kWaveM * rh * t.cpw * c.nrt + 220.0);
+                    const double waves = std::max(xcd_tiles * t.nmb / 32.0, 1.0) * wm * ks;
+                    if (!all && (std::max(waves, 6.0) + 0.325 * 6.0) * slots / 4.0 + 1650.0 + spread >= best.cost) continue;
                     t.rows_path = rows;
                     t.rh = rh;
                     t.groups = gr;
-                    t.rows_blk = std::min(rh * gr, c.Ho);
+                    t.rows_blk = rows_blk;
                     t.trows = (t.rows_blk - 1) * d.stride_h + d.KH;
                     t.wm = wm;
                     t.ks = ks;
-                    t.mblk = wm * kWaveM;
-                    t.nmb = (d.M + t.mblk - 1) / t.mblk;
                     t.tile_rows = gr * rh;
-                    // tile row stride: the columns a row needs, padded so that the rows of
-                    // neighbouring lane groups start on different LDS banks (row groups are
-                    // rh rows apart; their offset mod 32 banks should not be a multiple of
-                    // the lane stride I)
-                    t.tile_row = c.nqs * c.I + c.Kmax - 1;
-                    for (int pad = 0; pad < c.I && c.I > 1; ++pad)
-                        if ((rh * (t.tile_row + pad)) % 32 % c.I != 0) {
-                            t.tile_row += pad;
-                            break;
-                        }
+                    t.tile_row = tile_row;
                     t.lds_tile = (t.mblk * t.tile_rows * t.tile_row + 3) / 4 * 4;
                     t.lds_words = t.lds_tile;
                     if ((long)t.lds_words * 4 > kMaxLdsBytes) continue;
-                    t.cpw = (d.C + ks - 1) / ks;           // channels per slice
                     if (ks > 1 && (long)(ks - 1) * t.cpw >= d.C) continue;   // an empty slice
                     t.chk = t.cpw * ks;
-                    t.row_tiles = (c.Ho + t.rows_blk - 1) / t.rows_blk;
+                    t.row_tiles = row_tiles;
                     t.tiles = d.N * t.row_tiles * c.ncs;
                     t.kw_words = (int64_t)t.nmb * wm * ((int64_t)d.C * c.nrt + kStreamPad) * kWaveM;
-                    t.spread_words = (int64_t)d.N * d.C * c.Hp * c.ntw * c.nq;
                     if (!addressable(d, t)) {
                         range_limited = true;
                         continue;
@@ -247,18 +264,23 @@ bool place_launch(const samd_conv2d_desc &d, Conv2dGeom &c, i128 top_per_channel
                     // lanes read into the tile after every period, or widened in between:
                     // whichever is cheaper
                     const int64_t periods = set_period(t);
+                    const double bar = all ? 1e300 : best.cost - spread;
                     t.bias = t.result_signed ? t.msb_mask : 0;
                     t.two = 0;
                     t.odd_mask = 0;
-                    t.cost = multiply_cost(t, periods);
-                    Conv2dGeom w = t;
-                    w.two = wide_form(t, periods, top_per_channel, w.odd_mask);
-                    if (w.two) {
-                        w.cost = multiply_cost(w, periods);
-                        if (w.cost < t.cost) t = w;
+                    t.cost = multiply_cost(t, periods, bar);
+                    uint64_t odd_mask = 0;
+                    if (const int form = wide_form(t, periods, top_per_channel, odd_mask)) {
+                        t.two = form;
+                        const double cost = multiply_cost(t, periods, std::min(bar, t.cost));
+                        if (cost < t.cost) {
+                            t.odd_mask = odd_mask;
+                            t.cost = cost;
+                        } else {
+                            t.two = 0;
+                        }
                     }
-                    // the operand spread (the permanent-spacer layout has none)
-                    if (!t.layout_spaced) t.cost += (double)t.spread_words * (0.3 * c.I + 0.9) * 1e-6 * 587.5;
+                    t.cost += spread;
                     if (all) all->push_back(t);
                     if (t.cost < best.cost) {
                         best = t;
@@ -390,7 +412,7 @@ int search_lanes(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, int xoff, 
             // the multiply-adds alone, spread perfectly over every SIMD, bound the cost below
             const double floor_cost = 0.72 * (double)d.N * c.Ho * c.ncs * c.nqs * d.M * d.C * c.nrt / 64.0 / 1024.0;
             if (!all && found && floor_cost >= best.cost) continue;
-            if (!place_launch(d, c, (i128)d.KH * nj[c.nl - 1] * prod, all, range_limited)) continue;
+            if (!place_launch(d, c, (i128)d.KH * nj[c.nl - 1] * prod, all ? 1e300 : best.cost, all, range_limited)) continue;
             if (c.cost < best.cost) {
                 best = c;
                 found = true;

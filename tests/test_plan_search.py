@@ -1,0 +1,52 @@
+"""The planner's search on the CPU: a plan's first look-up prices only launches that may be
+the cheapest, and finds the one that pricing every launch finds."""
+import random
+import statistics
+import time
+
+import pytest
+
+import paper_1809_10572_amd as samd
+
+
+def _layers(count, seed):
+    rng = random.Random(seed)
+    for _ in range(count):
+        k, s = rng.choice((1, 3, 3, 5, 7, 11)), rng.choice((1, 1, 2, 4))
+        shape = (rng.randint(1, 8), rng.randint(3, 200), rng.randint(11, 120), rng.randint(11, 300), rng.randint(8, 200),
+                 k, k, s, s, k // 2, k // 2)
+        yield shape, samd.Fmt(rng.randint(1, 8), rng.random() < 0.5), samd.Fmt(rng.randint(1, 6), rng.random() < 0.8)
+
+
+def test_the_bounded_search_finds_the_cheapest_plan():
+    planned = 0
+    for shape, xf, wf in _layers(60, 3):
+        try:
+            plan = samd.conv2d_plan(shape, xf, wf)
+        except samd.SamdError:
+            continue
+        first, *rest = samd.conv2d_candidates(shape, xf, wf, 4)   # prices every launch
+        assert bytes(plan) == bytes(first), (shape, xf, wf)
+        assert all(plan.model_cost <= c.model_cost for c in rest)
+        planned += 1
+    assert planned > 40
+
+
+def _seconds(call, *args):
+    t = time.perf_counter()
+    call(*args)
+    return time.perf_counter() - t
+
+
+@pytest.mark.parametrize("shape,bits", [((8, 128, 56, 56, 128, 3, 3, 1, 1, 1, 1), 4),
+                                        ((4, 96, 40, 40, 64, 5, 5, 1, 1, 2, 2), 4),
+                                        ((4, 96, 40, 40, 64, 1, 1, 1, 1, 0, 0), 2)])
+def test_a_first_plan_prices_few_launches(shape, bits):
+    # against a listing, which prices every launch of the layer: 3 to 6 % of its time (15 to 40 %
+    # when every launch within reach of the multiply-adds' bound was priced in full)
+    xf, wf = samd.Fmt(bits, False), samd.Fmt(bits, True)
+    shares = []
+    for i in range(15):
+        new = shape[:4] + (shape[4] + i,) + shape[5:]     # a layer not planned yet
+        shares.append(_seconds(samd.conv2d_plan, new, xf, wf) / _seconds(samd.conv2d_candidates, new, xf, wf, 1))
+    assert statistics.median(shares) < 0.11, shares
