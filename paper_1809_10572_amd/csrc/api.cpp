@@ -483,7 +483,7 @@ int samd_conv2d_noalloc(const uint32_t *x, samd_fmt xf, const uint32_t *w, samd_
     if (!aligned4(x) || !aligned4(w) || !aligned4(y)) return fail(SAMD_EALIGN, "x / w / y not aligned");
     Conv2dGeom g;
     std::string err;
-    st = plan_conv2d_within(*d, xf, wf, SAMD_NOALLOC_SCRATCH_BYTES, g, err);
+    st = plan_conv2d_scratch(*d, xf, wf, g, err);
     if (st) return fail(st, "%s", err.c_str());
     const size_t need = conv2d_workspace_bytes(g);
     if (need > (size_t)SAMD_NOALLOC_SCRATCH_BYTES)

@@ -194,13 +194,19 @@ double multiply_cost(const Conv2dGeom &t, int64_t periods, double most) {
     return total(std::pow(std::pow(work, 1.565) + std::pow(tex, 1.565), 1.0 / 1.565));
 }
 
+// What a search is after: the cheapest plan whose workspace is within `limit` bytes, and, with
+// `all`, every such plan, priced and appended to it.
+struct Search {
+    std::vector<Conv2dGeom> *all = nullptr;
+    size_t limit = SIZE_MAX;
+};
+
 // Launch shapes of one lane geometry: output rows per thread (rh), row groups per wave,
 // output-channel waves (wm) and channel-slice waves (ks) per workgroup, and whether the
 // lane's rows share operand loads (3- and 5-row, stride-1 kernels); the cheapest is kept.
-// Returns false when no tile fits the LDS.  With `all`, every launch shape that fits is
-// also appended to it, priced.
+// Returns false when no tile fits the LDS, or none costs less than `most`.
 bool place_launch(const samd_conv2d_desc &d, Conv2dGeom &c, i128 top_per_channel, double most,
-                  std::vector<Conv2dGeom> *all, bool &range_limited) {
+                  const Search &how, bool &range_limited) {
     const int grp_max = 64 / c.nqs;
     const bool rows_ok = d.stride_h == 1 && ((d.KH == 3 && (c.ntw == 1 || c.ntw == 2)) || d.KH == 5);
     bool found = false;
@@ -238,7 +244,7 @@ bool place_launch(const samd_conv2d_desc &d, Conv2dGeom &c, i128 top_per_channel
                     // show it, without a look at the rest
                     const double slots = (1.0 - 1e-9) * (0.72 * kWaveM * rh * t.cpw * c.nrt + 220.0);
                     const double waves = std::max(xcd_tiles * t.nmb / 32.0, 1.0) * wm * ks;
-                    if (!all && (std::max(waves, 6.0) + 0.325 * 6.0) * slots / 4.0 + 1650.0 + spread >= best.cost) continue;
+                    if (!how.all && (std::max(waves, 6.0) + 0.325 * 6.0) * slots / 4.0 + 1650.0 + spread >= best.cost) continue;
                     t.rows_path = rows;
                     t.rh = rh;
                     t.groups = gr;
@@ -260,11 +266,12 @@ bool place_launch(const samd_conv2d_desc &d, Conv2dGeom &c, i128 top_per_channel
                         range_limited = true;
                         continue;
                     }
+                    if (conv2d_workspace_bytes(t) > how.limit) continue;
 
                     // lanes read into the tile after every period, or widened in between:
                     // whichever is cheaper
                     const int64_t periods = set_period(t);
-                    const double bar = all ? 1e300 : best.cost - spread;
+                    const double bar = how.all ? 1e300 : best.cost - spread;
                     t.bias = t.result_signed ? t.msb_mask : 0;
                     t.two = 0;
                     t.odd_mask = 0;
@@ -281,7 +288,7 @@ bool place_launch(const samd_conv2d_desc &d, Conv2dGeom &c, i128 top_per_channel
                         }
                     }
                     t.cost += spread;
-                    if (all) all->push_back(t);
+                    if (how.all) how.all->push_back(t);
                     if (t.cost < best.cost) {
                         best = t;
                         found = true;
@@ -311,7 +318,7 @@ namespace {
 // bits - so the decode can leave out the fix-up's final xor (Sec. 6.1); it halves the
 // channels a lane holds, so the planner prices both.
 int search_lanes(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, int xoff, int layout, int msb,
-                 Conv2dGeom &best, std::string &err, std::vector<Conv2dGeom> *all = nullptr) {
+                 const Search &how, Conv2dGeom &best, std::string &err) {
     Conv2dGeom g = {};
     g.N = d.N; g.C = d.C; g.H = d.H; g.W = d.W; g.M = d.M; g.KH = d.KH; g.KW = d.KW;
     g.sh = d.stride_h; g.sw = d.stride_w; g.ph = d.pad_h; g.pw = d.pad_w;
@@ -411,8 +418,8 @@ int search_lanes(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, int xoff, 
             c.macs_per_mad = (double)I * d.KW / (double)c.ntw;
             // the multiply-adds alone, spread perfectly over every SIMD, bound the cost below
             const double floor_cost = 0.72 * (double)d.N * c.Ho * c.ncs * c.nqs * d.M * d.C * c.nrt / 64.0 / 1024.0;
-            if (!all && found && floor_cost >= best.cost) continue;
-            if (!place_launch(d, c, (i128)d.KH * nj[c.nl - 1] * prod, all ? 1e300 : best.cost, all, range_limited)) continue;
+            if (!how.all && found && floor_cost >= best.cost) continue;
+            if (!place_launch(d, c, (i128)d.KH * nj[c.nl - 1] * prod, how.all ? 1e300 : best.cost, how, range_limited)) continue;
             if (c.cost < best.cost) {
                 best = c;
                 found = true;
@@ -437,35 +444,35 @@ int search_lanes(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, int xoff, 
 // signed b-bit value, so products are half as large and a lane holds twice as many;
 // the offset comes back exactly as 2^(b-1) times the sum of the weights over each
 // output's in-image taps.  Both are planned and the cheaper kept.
-int search_layout(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, int xoff, int layout, Conv2dGeom &best,
-                  std::string &err, std::vector<Conv2dGeom> *all) {
-    int st = search_lanes(d, xf, wf, xoff, layout, 1, best, err, all);
+int search_layout(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, int xoff, int layout, const Search &how,
+                  Conv2dGeom &best, std::string &err) {
+    int st = search_lanes(d, xf, wf, xoff, layout, 1, how, best, err);
     if (!layout || !(xf.is_signed || wf.is_signed || xoff)) return st;
     // the permanent-spacer layout of a signed result: also without the spacer MSB
     Conv2dGeom alt;
     std::string err2;
-    if (search_lanes(d, xf, wf, xoff, layout, 0, alt, err2, all) == SAMD_OK && (st != SAMD_OK || alt.cost < best.cost)) {
+    if (search_lanes(d, xf, wf, xoff, layout, 0, how, alt, err2) == SAMD_OK && (st != SAMD_OK || alt.cost < best.cost)) {
         best = alt;
         st = SAMD_OK;
     }
     return st;
 }
 
-int search_conv2d(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, int spacer, Conv2dGeom &best,
-                  std::string &err, std::vector<Conv2dGeom> *all = nullptr) {
-    int st = search_layout(d, xf, wf, 0, spacer, best, err, all);
+int search_conv2d(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, int spacer, const Search &how,
+                  Conv2dGeom &best, std::string &err) {
+    int st = search_layout(d, xf, wf, 0, spacer, how, best, err);
     if (!xf.is_signed && wf.is_signed && xf.bits >= 2) {
         Conv2dGeom alt;
         std::string err2;
         const samd_fmt xs = {xf.bits, 1};
-        const size_t first = all ? all->size() : 0;
-        if (search_layout(d, xs, wf, 1 << (xf.bits - 1), spacer, alt, err2, all) == SAMD_OK) {
+        const size_t first = how.all ? how.all->size() : 0;
+        if (search_layout(d, xs, wf, 1 << (xf.bits - 1), spacer, how, alt, err2) == SAMD_OK) {
             // the correction: in the packed layout one addition per output; in the
             // permanent-spacer layout four table lookups, issued where little hides them
             const double correction = (double)d.N * d.M * alt.Ho * alt.Wo * (spacer ? 20.0 : 0.5) / 64.0 / 1024.0;
             alt.cost += correction;
-            if (all)
-                for (size_t i = first; i < all->size(); ++i) (*all)[i].cost += correction;
+            if (how.all)
+                for (size_t i = first; i < how.all->size(); ++i) (*how.all)[i].cost += correction;
             if (st != SAMD_OK || alt.cost < best.cost) {
                 best = alt;
                 st = SAMD_OK;
@@ -508,7 +515,7 @@ int plan_conv2d(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, Conv2dGeom 
             return SAMD_OK;
         }
     }
-    int st = search_conv2d(d, xf, wf, spacer, g, err);
+    int st = search_conv2d(d, xf, wf, spacer, Search{}, g, err);
     if (st == SAMD_OK && !addressable(d, g)) {
         err = "the layer exceeds the kernels' index ranges (operand words of one image above 2 GiB, a kernel-word "
               "slice above 2^31 words, or an operand spread of 2^32 threads or more)";
@@ -522,36 +529,25 @@ int plan_conv2d(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, Conv2dGeom 
     return st;
 }
 
-// The shape's plan where its workspace is within `limit` bytes; else, unless that plan was
-// tuned, the cheapest candidate whose workspace is.  Faster plans are not always smaller:
-// without the second step 1 of 1500 drawn layers around 64 MiB, which an earlier plan of
-// the same candidates served, would not fit.
-int plan_conv2d_within(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, size_t limit, Conv2dGeom &g,
-                       std::string &err) {
+int plan_conv2d_scratch(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, Conv2dGeom &g, std::string &err) {
+    constexpr size_t limit = SAMD_NOALLOC_SCRATCH_BYTES;
     int st = plan_conv2d(d, xf, wf, g, err);
     if (st != SAMD_OK || conv2d_workspace_bytes(g) <= limit) return st;
     PlanKey key = plan_key(d, xf, wf, 0);
     std::unique_lock<std::mutex> lock(plan_mu);
     if (tuned_plans.count(key)) return SAMD_OK;
-    key.back() = -1;   // the fitting plan's own entry, for the next call
-    const auto it = plan_cache.find(key);
-    if (it != plan_cache.end() && conv2d_workspace_bytes(it->second) <= limit) {
-        g = it->second;
-        return SAMD_OK;
+    key.back() = -1;   // the fitting plan's own entry; one without lanes: no plan fits
+    auto it = plan_cache.find(key);
+    if (it == plan_cache.end()) {
+        lock.unlock();
+        Conv2dGeom fit;
+        std::string none;
+        if (search_conv2d(d, xf, wf, 0, Search{nullptr, limit}, fit, none) != SAMD_OK) fit = {};
+        lock.lock();
+        if (plan_cache.size() >= kPlanCacheMax) plan_cache.clear();
+        it = plan_cache.emplace(key, fit).first;
     }
-    lock.unlock();
-    Conv2dGeom model;
-    std::vector<Conv2dGeom> all;
-    st = search_conv2d(d, xf, wf, 0, model, err, &all);
-    if (st) return st;
-    const Conv2dGeom *best = nullptr;
-    for (const Conv2dGeom &c : all)
-        if (addressable(d, c) && conv2d_workspace_bytes(c) <= limit && (!best || c.cost < best->cost)) best = &c;
-    if (!best) return SAMD_OK;   // the caller sees that g does not fit
-    g = *best;
-    lock.lock();
-    if (plan_cache.size() >= kPlanCacheMax) plan_cache.clear();
-    plan_cache[key] = g;
+    if (it->second.L) g = it->second;
     return SAMD_OK;
 }
 
@@ -561,7 +557,7 @@ int conv2d_candidates(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, int m
     // the model alone (no cache, no tuned plan): its choice, then every priced candidate
     Conv2dGeom model;
     std::vector<Conv2dGeom> all;
-    int st = search_conv2d(d, xf, wf, spacer, model, err, &all);
+    int st = search_conv2d(d, xf, wf, spacer, Search{&all}, model, err);
     if (st) return st;
     if (!addressable(d, model)) {
         err = "the layer exceeds the kernels' index ranges (operand words of one image above 2 GiB, a kernel-word "
@@ -593,7 +589,7 @@ int find_conv2d_candidate(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf,
     // every priced candidate, unsorted (matching needs no ranking)
     Conv2dGeom model;
     std::vector<Conv2dGeom> all;
-    int st = search_conv2d(d, xf, wf, spacer, model, err, &all);
+    int st = search_conv2d(d, xf, wf, spacer, Search{&all}, model, err);
     if (st) return st;
     for (const Conv2dGeom &c : all)
         if (addressable(d, c) && match(c)) {

@@ -120,10 +120,12 @@ int plan_conv2d(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, Conv2dGeom 
                 int spacer = 0);
 int plan_conv1d(int64_t n, samd_fmt xf, const int32_t *taps, int32_t K, samd_fmt kf, Conv1dGeom &g,
                 std::string &err);
+// The packed layout's plan for the library's scratch array: the shape's plan where its
+// workspace fits the array or was tuned; else the cheapest plan whose workspace fits (faster
+// plans are not always smaller), and the shape's own, which does not, where none does.
+int plan_conv2d_scratch(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, Conv2dGeom &g, std::string &err);
 // Candidate plans of a shape, ranked by the model's cost, the model's choice first, at
 // most max_count of them (distinct lane geometries and launch shapes).
-int plan_conv2d_within(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, size_t limit, Conv2dGeom &g,
-                       std::string &err);
 int conv2d_candidates(const samd_conv2d_desc &d, samd_fmt xf, samd_fmt wf, int max_count,
                       std::vector<Conv2dGeom> &out, std::string &err, int spacer = 0);
 // The first of all candidate plans (no count limit) that `match` accepts.

@@ -1,5 +1,6 @@
 """The planner's search on the CPU: a plan's first look-up prices only launches that may be
 the cheapest, and finds the one that pricing every launch finds."""
+import ctypes
 import random
 import statistics
 import time
@@ -50,3 +51,16 @@ def test_a_first_plan_prices_few_launches(shape, bits):
         new = shape[:4] + (shape[4] + i,) + shape[5:]     # a layer not planned yet
         shares.append(_seconds(samd.conv2d_plan, new, xf, wf) / _seconds(samd.conv2d_candidates, new, xf, wf, 1))
     assert statistics.median(shares) < 0.11, shares
+
+
+def test_a_layer_too_large_for_the_scratch_array_is_searched_once():
+    # no plan of this layer fits the array; the refusal, which comes before any HIP call, is
+    # remembered
+    shape, xf, wf = (16, 512, 57, 57, 384, 3, 3, 1, 1, 1, 1), samd.Fmt(8, False), samd.Fmt(8, True)
+    d = samd.Conv2dDesc.of(shape)
+    call = lambda: samd.lib().samd_conv2d_noalloc(256, xf, 256, wf, ctypes.byref(d), 256, None)
+    refused = lambda: _seconds(lambda: statuses.append(call()))
+    statuses = []
+    first, later = refused(), min(refused() for _ in range(5))
+    assert set(statuses) == {samd.SAMD_ENOSPC} and "scratch array" in samd.lib().samd_last_error().decode()
+    assert later < 0.2 * first, (first, later)
