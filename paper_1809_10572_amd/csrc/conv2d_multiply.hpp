@@ -148,8 +148,9 @@ __device__ __forceinline__ void decode_word_n(uint64_t v, uint64_t msb_mask, int
 // lane below the top one), so every such lane is a non-negative field, and
 //     odd  += (V >> L) & odd_mask        lanes 1, 3, ... as fields 2 L bits apart
 //     all  += V                          (mod 2^64; all - (odd << L) is lanes 0, 2, ...)
-// are two 64-bit sums whose fields have 2 L bits: room for 2^L such steps.  Five to seven
-// full-rate instructions per accumulator instead of about 22 and one LDS atomic per lane.
+// are two 64-bit sums whose fields have 2 L bits: room for 2^L such steps.  Six
+// instructions per accumulator (a shift, two ands, two 64-bit adds, the restart), eight with
+// the top lane apart, instead of about 22 and one LDS atomic per lane.
 // The sums are decoded into the tile once, after the wave's last channel.
 // TWO == 1: the top lane's sum over the whole slice fits the top bits of the word it ends
 // in.  TWO == 2: it does not, and is summed in a register of its own.
@@ -166,26 +167,26 @@ struct WideLanes {
     }
 
     // offset: `steps` times half a lane's range, taken off every biased lane; field: 2 L
-    // low bits (all 32 when 2 L >= 32: sums are taken mod 2^32)
+    // low bits (all 32 when 2 L >= 32).  Both mod 2^32, as the outputs are
     template <int NL>
-    __device__ __forceinline__ void decode(int L, uint32_t field, int32_t offset, uint32_t at) const {
+    __device__ __forceinline__ void decode(int L, uint32_t field, uint32_t offset, uint32_t at) const {
         const uint64_t even = all - (odd << L);
 #pragma unroll
         for (int j = 0; j < NL - 1; ++j) {
             const uint64_t w = (j & 1) ? odd >> ((j - 1) * L) : even >> (j * L);
-            tile_add(at, j, (int32_t)((uint32_t)w & field) - offset);
+            tile_add(at, j, (int32_t)(((uint32_t)w & field) - offset));
         }
         tile_add(at, NL - 1, TWO == 2 ? top
                                       : (int32_t)((NL & 1) ? (int64_t)even >> ((NL - 1) * L)
                                                            : (int64_t)odd >> ((NL - 2) * L)));
     }
 
-    __device__ __forceinline__ void decode_n(int L, int nl, uint32_t field, int32_t offset, uint32_t at) const {
+    __device__ __forceinline__ void decode_n(int L, int nl, uint32_t field, uint32_t offset, uint32_t at) const {
         const uint64_t even = all - (odd << L);
 #pragma unroll 1
         for (int j = 0; j < nl - 1; ++j) {
             const uint64_t w = (j & 1) ? odd >> ((j - 1) * L) : even >> (j * L);
-            tile_add(at, j, (int32_t)((uint32_t)w & field) - offset);
+            tile_add(at, j, (int32_t)(((uint32_t)w & field) - offset));
         }
         tile_add(at, nl - 1, TWO == 2 ? top
                                       : (int32_t)((nl & 1) ? (int64_t)even >> ((nl - 1) * L)
@@ -381,7 +382,7 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
                     SAMD_DECODE_ADDRESSES
                     const int L = d->L;
                     const uint32_t field = 2 * L >= 32 ? 0xffffffffu : (1u << (2 * L)) - 1;
-                    const int32_t offset = SG ? steps << (L - 1) : 0;
+                    const uint32_t offset = SG ? (uint32_t)steps << (L - 1) : 0;
 #define SAMD_WIDE_NL(NL_)                                                                             \
     case NL_:                                                                                         \
         SAMD_DECODE_LOOP((wide[r][m].template decode<NL_>(L, field, offset, at)))                     \
@@ -803,9 +804,11 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
     }
 }
 
-// x / d = (x * mul) >> 16 for the lanes and waves it is used on: exact while x d < 65536
-// (64 lanes by up to 64 words, 16 waves by up to 256 rows)
+// x / d = (x * mul) >> 16 for the small numbers it is used on: exact while x d < 65536 (lanes
+// by words of a row, and the tile rows a workgroup copies at once - up to 8 a wave - by the
+// rows of a tile, at most 4 of each of a wave's lane groups)
 inline int32_t small_reciprocal(int d) { return 65536 / d + 1; }
+static_assert(64 * 64 < 65536 && kMaxBlockWaves * 8 * (64 * 4) < 65536, "small_reciprocal");
 
 template <int RH, int KHT, int TWO, bool SG, bool SEG>
 int launch_multiply_instance(const Conv2dGeom &g, int32_t *y, const void *ws, hipStream_t s, const int32_t *src) {
