@@ -177,9 +177,15 @@ def _check(status: int) -> None:
         raise SamdError(status, L.samd_status_str(status).decode(), L.samd_last_error().decode())
 
 
+# the raw handle, without the Stream object around it (0.2 instead of 2 us a call), where this
+# torch has the accessor
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(t: torch.Tensor) -> int:
-    # the raw handle, without the Stream object around it (0.2 instead of 2 us a call)
-    return torch._C._cuda_getCurrentRawStream(t.get_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream(t.device).cuda_stream
+    return _raw_stream(t.get_device())
 
 
 def _on_gpu(t: torch.Tensor) -> bool:

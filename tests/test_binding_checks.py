@@ -152,3 +152,15 @@ def test_conv1d_unpack_and_int8_check_sizes(fake):
     expect_refused(rec, samd.conv2d_int8, t(xn - 1, torch.uint8), XF, t(wn, torch.int8), WF, SHAPE, ws=ws, out=y)
     expect_refused(rec, samd.conv2d_int8, t(xn, torch.uint8), XF, t(wn - 1, torch.int8), WF, SHAPE, ws=ws, out=y)
     expect_refused(rec, samd.conv2d_int8_prepared, t(xn - 1, torch.uint8), XF, WF, SHAPE, ws, out=y)
+
+
+def test_stream_without_the_raw_accessor(monkeypatch):
+    # a torch without the private accessor: the public call, for the tensor's device
+    class Stream:
+        cuda_stream = 77
+
+    asked = []
+    monkeypatch.setattr(samd, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: asked.append(device) or Stream)
+    x = torch.zeros(1)
+    assert samd._stream(x) == 77 and asked == [x.device]
