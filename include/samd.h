@@ -162,6 +162,27 @@ int samd_conv1d_plan_query(int64_t n, samd_fmt xf, const int32_t *taps, int32_t 
 int samd_conv2d_plan_query(const samd_conv2d_desc *d, samd_fmt xf, samd_fmt wf,
                            samd_conv2d_plan *out);
 
+/* Which form of the multiply kernel a plan runs, and when its lanes are read (host-only query,
+ * for inspection and tests).
+ *   kernel_rows  3 or 5: output rows share operand loads; 1: batches of three steps that never
+ *                straddle channels; 0: any other layer
+ *   widened      0: lanes are decoded into the output tile after every period; 1, 2: widened in
+ *                registers after every period and decoded once (2: the top lane is summed apart)
+ *   period       batches between two reads of the lanes (kernel words of a channel where
+ *                kernel_rows is 3 or 5, else batches of three steps, or -steps where the lanes
+ *                hold fewer steps than a batch); a step is one kernel word of one kernel row
+ *   result_signed 1: lanes are sign-extended
+ *   odd_mask     widened != 0: the lanes 1, 3, ... of an accumulator shifted right by one lane */
+typedef struct {
+    int32_t kernel_rows, widened, period, result_signed;
+    uint64_t odd_mask;
+} samd_conv2d_form;
+
+/* Host-only: the form of the layer's current plan; layout_spaced 1 asks for the
+ * permanent-spacer layout's. */
+int samd_conv2d_form_query(const samd_conv2d_desc *d, samd_fmt xf, samd_fmt wf, int32_t layout_spaced,
+                           samd_conv2d_form *out);
+
 /* Library utility: the workspace bytes samd_conv2d and its split entry points need for
  * (xf, wf, *d) under the shape's current plan (kernel-word streams, the recentring
  * correction table, the multiply kernel's ticket counters and the staged operand words).

@@ -16,7 +16,8 @@ from typing import List, Optional, Sequence, Tuple
 import torch
 
 __all__ = ["Fmt", "Conv2dDesc", "Conv1dPlan", "Conv2dPlan", "SamdError", "lib", "row_words", "pack", "unpack", "conv1d",
-           "conv1d_plan", "conv2d_plan", "conv2d_candidates", "conv2d_tune_workspace", "conv2d_tune", "conv2d_untune",
+           "conv1d_plan", "conv2d_plan", "Conv2dForm", "conv2d_form",
+           "conv2d_candidates", "conv2d_tune_workspace", "conv2d_tune", "conv2d_untune",
            "conv2d_use_plan", "plan_key",
            "conv2d_workspace", "conv2d", "conv2d_noalloc", "conv2d_prepare", "conv2d_prepared",
            "conv2d_stage", "conv2d_accumulate",
@@ -67,6 +68,11 @@ class Conv2dPlan(ctypes.Structure):
                 ("layout_spaced", ctypes.c_int32), ("spacer_msb", ctypes.c_int32)]
 
 
+class Conv2dForm(ctypes.Structure):
+    _fields_ = [("kernel_rows", ctypes.c_int32), ("widened", ctypes.c_int32), ("period", ctypes.c_int32),
+                ("result_signed", ctypes.c_int32), ("odd_mask", ctypes.c_uint64)]
+
+
 class SpacedLayout(ctypes.Structure):
     _fields_ = [("lane_bits", ctypes.c_int32), ("lanes", ctypes.c_int32), ("words_per_row", ctypes.c_int32),
                 ("tap_words", ctypes.c_int32), ("padded_rows", ctypes.c_int32), ("x_offset", ctypes.c_int32),
@@ -112,6 +118,8 @@ def lib():
             "samd_conv1d_plan_query": (ctypes.c_int, [_i64, Fmt, _p, _i32, Fmt, ctypes.POINTER(Conv1dPlan)]),
             "samd_conv2d_plan_query": (ctypes.c_int, [ctypes.POINTER(Conv2dDesc), Fmt, Fmt,
                                                       ctypes.POINTER(Conv2dPlan)]),
+            "samd_conv2d_form_query": (ctypes.c_int, [ctypes.POINTER(Conv2dDesc), Fmt, Fmt, _i32,
+                                                      ctypes.POINTER(Conv2dForm)]),
             "samd_conv2d_workspace": (ctypes.c_int, [ctypes.POINTER(Conv2dDesc), Fmt, Fmt, ctypes.POINTER(_sz)]),
             "samd_conv2d": (ctypes.c_int, [_p, Fmt, _p, Fmt, ctypes.POINTER(Conv2dDesc), _p, _p, _sz, _p]),
             "samd_conv2d_prepare": (ctypes.c_int, [_p, Fmt, ctypes.POINTER(Conv2dDesc), Fmt, _p, _sz, _p]),
@@ -305,6 +313,14 @@ def conv2d_plan(shape, xfmt: Fmt, wfmt: Fmt) -> Conv2dPlan:
     plan = Conv2dPlan()
     _check(lib().samd_conv2d_plan_query(ctypes.byref(Conv2dDesc.of(shape)), xfmt, wfmt, ctypes.byref(plan)))
     return plan
+
+
+def conv2d_form(shape, xfmt: Fmt, wfmt: Fmt, spaced: bool = False) -> Conv2dForm:
+    """The form of the multiply kernel the layer's current plan runs (of the packed layout, or
+    of the permanent-spacer one)."""
+    form = Conv2dForm()
+    _check(lib().samd_conv2d_form_query(ctypes.byref(Conv2dDesc.of(shape)), xfmt, wfmt, int(spaced), ctypes.byref(form)))
+    return form
 
 
 def conv2d_workspace(shape, xfmt: Fmt, wfmt: Fmt) -> int:

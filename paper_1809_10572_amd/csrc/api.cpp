@@ -231,6 +231,23 @@ int samd_conv2d_plan_query(const samd_conv2d_desc *d, samd_fmt xf, samd_fmt wf, 
     return SAMD_OK;
 }
 
+int samd_conv2d_form_query(const samd_conv2d_desc *d, samd_fmt xf, samd_fmt wf, int32_t layout_spaced,
+                           samd_conv2d_form *out) {
+    set_error("");
+    int st = check_fmt(xf, "xf");
+    if (!st) st = check_fmt(wf, "wf");
+    if (!st) st = check_conv2d_desc(d);
+    if (!st) st = check_overflow(d, xf, wf);
+    if (st) return st;
+    if (!out) return fail(SAMD_EINVAL, "out must not be NULL");
+    Conv2dGeom g;
+    std::string err;
+    st = plan_conv2d(*d, xf, wf, g, err, layout_spaced ? 1 : 0);
+    if (st) return fail(st, "%s", err.c_str());
+    *out = samd_conv2d_form{conv2d_kernel_rows(g), g.two, g.period, g.result_signed, g.odd_mask};
+    return SAMD_OK;
+}
+
 int samd_conv2d_workspace(const samd_conv2d_desc *d, samd_fmt xf, samd_fmt wf, size_t *bytes) {
     set_error("");
     int st = check_fmt(xf, "xf");

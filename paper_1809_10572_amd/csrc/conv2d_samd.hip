@@ -166,14 +166,12 @@ int resident_workgroups(const void *kernel, int block, size_t shm, int &out) {
 
 int launch_conv2d_multiply(const Conv2dGeom &g, int32_t *y, const void *ws, hipStream_t s, const int32_t *src) {
     int st = kNoInstance;
-    if (!g.rows_path)
-        st = g.nrt % kStepBatch == 0 ? launch_multiply_batches(g, y, ws, s, src) : launch_multiply_general(g, y, ws, s, src);
-    else if (g.KH == 5)
-        st = launch_multiply_rows5(g, y, ws, s, src);
-    else if (g.two)
-        st = launch_multiply_rows3_wide(g, y, ws, s, src);
-    else
-        st = launch_multiply_rows3(g, y, ws, s, src);
+    switch (conv2d_kernel_rows(g)) {
+        case 0: st = launch_multiply_general(g, y, ws, s, src); break;
+        case 1: st = launch_multiply_batches(g, y, ws, s, src); break;
+        case 3: st = g.two ? launch_multiply_rows3_wide(g, y, ws, s, src) : launch_multiply_rows3(g, y, ws, s, src); break;
+        case 5: st = launch_multiply_rows5(g, y, ws, s, src); break;
+    }
     if (st != kNoInstance) return st;
     set_error("conv2d: no kernel for this geometry");
     return SAMD_EUNSUPPORTED;

@@ -101,6 +101,10 @@ struct Conv2dGeom {
 // weights per output channel; the permanent-spacer layout is defined with 0 there.
 inline constexpr int32_t conv2d_pad_value(int32_t xoff, int32_t layout_spaced) { return layout_spaced ? 0 : -xoff; }
 
+// The multiply kernel's form: 3 or 5 (rows that share loads), 1 (channels of whole batches of
+// steps), 0 (any other layer).
+inline int conv2d_kernel_rows(const Conv2dGeom &g) { return g.rows_path ? g.KH : g.nrt % kStepBatch == 0 ? 1 : 0; }
+
 // 1-D convolution geometry (unsigned operands, 32x32 -> 64-bit products).
 struct Conv1dGeom {
     int64_t n, nout, nwords;        // inputs, outputs, output words

@@ -1,8 +1,11 @@
 """Every form of the multiply kernel - rows shared by 3- and 5-row kernels, the general
 path, lanes decoded every period or widened in registers (two-level lanes, with the top
-lane inside its word and apart), column segments - against the oracle, bit-exact, at
-shapes where each begins or ends: odd channel counts and slices, periods of one batch, rows
-past the image, filters past M, and operands that drive every lane to its bound."""
+lane inside its word and apart), signed and unsigned results, column segments - against the
+oracle, bit-exact, at shapes where each begins or ends: odd channel counts and slices,
+periods of one batch or less, rows past the image, filters past M, and operands that drive
+every lane to its bound."""
+import itertools
+
 import numpy as np
 import pytest
 import torch
@@ -32,13 +35,13 @@ CASES = [
 ]
 
 
-def _operands(kind, shape, xb, xs, wb):
+def _operands(kind, shape, xb, xs, wb, ws=True):
     N, C, H, W, M, KH, KW = shape[:7]
     xlo, xhi = wl.value_range(xb, xs)
-    wlo, whi = wl.value_range(wb, True)
+    wlo, whi = wl.value_range(wb, ws)
     if kind == "mixed":
         rng = np.random.default_rng(sum(shape) + xb)
-        return wl.half_extremes(rng, (N, C, H, W), xb, xs), wl.half_extremes(rng, (M, C, KH, KW), wb, True)
+        return wl.half_extremes(rng, (N, C, H, W), xb, xs), wl.half_extremes(rng, (M, C, KH, KW), wb, ws)
     x = xlo if kind == "low" else xhi       # every product at one extreme
     return np.full((N, C, H, W), x), np.full((M, C, KH, KW), wlo if kind != "high" else whi)
 
@@ -75,6 +78,8 @@ def test_every_candidate_matches_the_oracle(case, kind):
             try:
                 samd.conv2d_use_plan(shape, xf, wf, p)
             except samd.SamdError:
+                if not isinstance(p, dict):
+                    raise           # a listed plan
                 continue            # a launch shape this layer does not have
             ran += 1
             y = samd.conv2d(xp, xf, wp, wf, shape)
@@ -85,9 +90,96 @@ def test_every_candidate_matches_the_oracle(case, kind):
     assert ran >= len(cands) // 4
 
 
+# Layers that between them run every instance of the kernel: (shape, x bits, x signed, w bits,
+# w signed) and the forms of each, as (kernel_rows, rows per lane, widened) of a plan.
+# Result signedness and column segments (the rows of 261 columns) are the layer's own.
+ROWS3 = set(itertools.product((1, 3), (1, 2), (0, 1, 2))) | {(3, 3, 0), (3, 4, 0)}
+ROWS5 = set(itertools.product((0, 5), (1, 2), (0, 1, 2)))
+FORMS = [
+    ((1, 47, 7, 19, 9, 3, 3, 1, 1, 1, 1), 4, False, 4, True, ROWS3),
+    ((1, 47, 7, 19, 9, 3, 3, 1, 1, 1, 1), 8, False, 8, False, ROWS3),
+    ((1, 47, 7, 261, 9, 3, 3, 1, 1, 1, 1), 8, False, 8, False, ROWS3),
+    ((1, 97, 5, 261, 9, 3, 3, 1, 1, 1, 1), 8, True, 8, True, ROWS3),
+    ((1, 47, 7, 19, 9, 5, 5, 1, 1, 2, 2), 3, False, 3, False, ROWS5),
+    ((1, 47, 7, 19, 9, 5, 5, 1, 1, 2, 2), 4, False, 4, True, {f for f in ROWS5 if f[2] < 2}),
+    ((1, 47, 7, 19, 9, 5, 5, 1, 1, 2, 2), 8, True, 8, True, {(5, 1, 2), (5, 2, 2)}),
+    ((1, 47, 7, 19, 9, 7, 7, 1, 1, 3, 3), 8, True, 8, True, {(0, 1, 2), (0, 2, 2)}),
+    ((1, 47, 7, 261, 9, 5, 5, 1, 1, 2, 2), 4, False, 4, True, {f for f in ROWS5 if f[2] < 2}),
+    ((1, 47, 7, 261, 9, 5, 5, 1, 1, 2, 2), 8, True, 8, True, {(5, 1, 2), (5, 2, 2)}),
+    ((1, 47, 7, 261, 9, 7, 7, 1, 1, 3, 3), 8, True, 8, True, {(0, 1, 2), (0, 2, 2)}),
+    ((1, 47, 7, 261, 9, 5, 5, 1, 1, 2, 2), 4, False, 4, False,
+     {f for f in ROWS5 if f[2] < 2} - {(0, 2, 0)} | {(5, 1, 2)}),
+    ((1, 47, 7, 261, 9, 5, 5, 1, 1, 2, 2), 8, False, 8, False, {(5, 2, 2)}),
+    ((1, 47, 7, 261, 9, 7, 7, 1, 1, 3, 3), 7, False, 7, False, {(0, 1, 2), (0, 2, 0), (0, 2, 2)}),
+]
+
+
+def form_plans(case):
+    """Plans of a layer of FORMS, the first found of each of its forms."""
+    shape, xb, xs, wb, ws, forms = FORMS[case]
+    xf, wf = samd.Fmt(xb, xs), samd.Fmt(wb, ws)
+    found = {}
+    try:
+        for k in map(lambda p: p if isinstance(p, dict) else samd.plan_key(p),
+                     _variants(samd.conv2d_candidates(shape, xf, wf, samd.MAX_CANDIDATES))):
+            try:
+                samd.conv2d_use_plan(shape, xf, wf, k)
+            except samd.SamdError:
+                continue
+            f = samd.conv2d_form(shape, xf, wf)
+            assert f.result_signed == (xs or ws)
+            found.setdefault((f.kernel_rows, k["rows_per_thread"], f.widened), k)
+            if forms <= set(found):
+                break
+    finally:
+        samd.conv2d_untune(shape, xf, wf)
+    return {f: found.get(f) for f in sorted(forms)}
+
+
+@pytest.mark.parametrize("case", range(len(FORMS)))
+def test_every_form_matches_the_oracle(case):
+    shape, xb, xs, wb, ws, _ = FORMS[case]
+    xf, wf = samd.Fmt(xb, xs), samd.Fmt(wb, ws)
+    plans = form_plans(case)
+    assert None not in plans.values(), plans
+    dev = lambda a, s: torch.from_numpy(a.astype(np.int8 if s else np.uint8)).to(DEV)
+    runs = []
+    for kind in ("mixed", "low", "high", "opposite"):
+        x, w = _operands(kind, shape, xb, xs, wb, ws)
+        runs.append((kind, samd.pack(dev(x, xs), xb, xs), samd.pack(dev(w, ws), wb, ws), ref.conv2d(x, w, shape)))
+    try:
+        for form, key in plans.items():
+            samd.conv2d_use_plan(shape, xf, wf, key)
+            for kind, xp, wp, want in runs:
+                y = samd.conv2d(xp, xf, wp, wf, shape)
+                np.testing.assert_array_equal(y.cpu().numpy(), want, err_msg=f"{form} {kind} {key}")
+    finally:
+        samd.conv2d_untune(shape, xf, wf)
+
+
+# default plans whose lanes hold two, or one, product: (shape, formats, steps)
+FEW_STEPS = [
+    ((1, 7, 25, 35, 138, 1, 1, 1, 1, 0, 0), (2, False), (2, True), 2),
+    ((2, 2, 33, 22, 155, 1, 1, 1, 1, 0, 0), (4, True), (2, True), 1),
+    ((2, 7, 33, 78, 168, 1, 1, 1, 1, 0, 0), (2, True), (7, False), 1),
+]
+
+
+@pytest.mark.parametrize("shape,xfmt,wfmt,steps", FEW_STEPS)
+def test_default_plans_of_few_steps_per_decode(shape, xfmt, wfmt, steps):
+    xf, wf = samd.Fmt(*xfmt), samd.Fmt(*wfmt)
+    assert samd.conv2d_form(shape, xf, wf).period == -steps
+    x, w = _operands("mixed", shape, *xfmt, *wfmt)
+    want = ref.conv2d(x, w, shape)
+    dev = lambda a, s: torch.from_numpy(a.astype(np.int8 if s else np.uint8)).to(DEV)
+    y = samd.conv2d(samd.pack(dev(x, xfmt[1]), *xfmt), xf, samd.pack(dev(w, wfmt[1]), *wfmt), wf, shape)
+    np.testing.assert_array_equal(y.cpu().numpy(), want)
+
+
 def test_few_steps_per_decode_on_the_general_path():
     # one-bit 1x1 layers list lane geometries that hold fewer products than one batch of
-    # three steps; every listed one of the narrowest lanes is run
+    # three steps (2-bit lanes, one product) or one batch (3-bit lanes); every listed one of
+    # the narrowest lanes is run
     shape, xf, wf = (1, 13, 3, 20, 8, 1, 1, 1, 1, 0, 0), samd.Fmt(1, False), samd.Fmt(1, True)
     rng = np.random.default_rng(5)
     x = wl.uniform(rng, (1, 13, 3, 20), 1, False)
@@ -96,7 +188,7 @@ def test_few_steps_per_decode_on_the_general_path():
     xp = samd.pack(torch.from_numpy(x.astype(np.uint8)).to(DEV), 1, False)
     wp = samd.pack(torch.from_numpy(w.astype(np.int8)).to(DEV), 1, True)
     seen = set()
-    for bits in (3, 4, 5):
+    for bits in (2, 3, 4, 5):
         for lanes in range(2, 9):
             for rows in (1, 2, 3):
                 for ks in (1, 2):
@@ -106,12 +198,12 @@ def test_few_steps_per_decode_on_the_general_path():
                         samd.conv2d_use_plan(shape, xf, wf, key)
                     except samd.SamdError:
                         continue
-                    seen.add(samd.conv2d_plan(shape, xf, wf).flush_channels)
+                    seen.add(samd.conv2d_form(shape, xf, wf).period)
                     y = samd.conv2d(xp, xf, wp, wf, shape)
                     torch.cuda.synchronize()
                     samd.conv2d_untune(shape, xf, wf)
                     np.testing.assert_array_equal(y.cpu().numpy(), want, err_msg=str(key))
-    assert min(seen) >= 1
+    assert {-1, 1} <= seen
 
 
 def test_a_layer_whose_fastest_plan_passes_the_scratch_array_still_runs_there():
@@ -134,7 +226,7 @@ def test_a_layer_whose_fastest_plan_passes_the_scratch_array_still_runs_there():
 @pytest.mark.parametrize("bits,signed", [(8, False), (3, True)])
 def test_rows_written_several_at_a_time(width, bits, signed):
     # 8, 4 or 2 output rows leave a wave at once up to 8, 16 and 32 columns; 13 filters and 11
-    # rows leave tiles, channel blocks and lanes part empty; 8-bit plans are recentred
+    # rows leave channel blocks and lanes part empty
     shape, xf, wf = (3, 6, 11, width, 13, 3, 3, 1, 1, 1, 1), samd.Fmt(bits, signed), samd.Fmt(bits, True)
     x, w = _operands("mixed", shape, bits, signed, bits)
     want = torch.from_numpy(np.asarray(ref.conv2d(x, w, shape))).to(DEV, torch.int32)

@@ -5,7 +5,10 @@ operand word I, kernel-word tap groups, channels per decode G) is replayed here 
 Python, independently of the HIP code: operand and kernel words must be int32, the
 64-bit accumulator must hold every partial sum, and decoding the lanes with the fix-up
 of the signed-convolution figure must give the direct sums - for extreme inputs at the
-bound, and for a complete small convolution compared with the oracle."""
+bound, and for a complete small convolution compared with the oracle, which follows the
+multiply kernel's form: its order of steps, when it reads the lanes, and how (decoded, or
+widened and decoded at the end)."""
+import functools
 import itertools
 import random
 
@@ -16,6 +19,7 @@ import paper_1809_10572_amd as samd
 import samd_workloads as wl
 from oracle import reference as ref
 from oracle import samd_model as sm
+import test_gpu_multiply_forms as multiply
 
 I32 = (-(1 << 31), (1 << 31) - 1)
 
@@ -38,48 +42,98 @@ def decode_lanes(V, L, nl, signed):
     return lanes + [V >> ((nl - 1) * L)]
 
 
-def planned_conv2d(x, w, shape, xf, wf, plan):
+def odd_lanes(L, nl):
+    """The lanes 1, 3, ... of an accumulator shifted right by one lane; the top lane has every
+    bit above its first."""
+    mask = sum(((1 << L) - 1) << ((j - 1) * L) for j in range(1, nl - 1, 2))
+    if nl % 2 == 0:
+        mask |= (1 << 64) - (1 << ((nl - 2) * L))
+    return mask
+
+
+def read_slice(words, plan, form):
+    """Lane sums of one wave's slice of the channels: words holds, per channel, the products of
+    its steps (kernel row ky, kernel word t), and the accumulator is read after every period."""
+    L, nl = plan.lane_bits, plan.out_lanes
+    top, M64 = (nl - 1) * L, (1 << 64) - 1
+    if form.kernel_rows >= 3:     # a batch: one kernel word of one channel, all its kernel rows
+        batches = [sum(w[ky][t] for ky in range(len(w))) for w in words for t in range(plan.tap_words)]
+        size = form.period
+    else:                         # batches of three steps, or periods of fewer
+        batches = [p for w in words for row in w for p in row]
+        size = 3 * form.period if form.period > 0 else -form.period
+    # accumulators of signed results start with half a lane's range in every lane below the top
+    bias = sum(1 << (j * L + L - 1) for j in range(nl - 1)) if form.result_signed else 0
+    lanes, every, odd, apart, reads = [0] * nl, 0, 0, 0, 0
+    for i in range(0, len(batches), size):
+        v = bias + sum(batches[i:i + size])
+        assert -(1 << 63) <= v < (1 << 63)
+        reads += 1
+        if form.widened:
+            every, odd, apart = (every + v) & M64, (odd + ((v >> L) & form.odd_mask)) & M64, apart + (v >> top)
+        elif form.result_signed:
+            fixed = (v & M64) ^ bias
+            got = sm.word_to_lanes(fixed, L, nl - 1, signed=True) + [sm.to_signed(fixed, 64) >> top]
+            lanes = [a + b for a, b in zip(lanes, got)]
+        else:
+            lanes = [a + b for a, b in zip(lanes, decode_lanes(v, L, nl, False))]
+    if form.widened:
+        even = (every - (odd << L)) & M64
+        field = min(2 * L, 32)
+        offset = reads << (L - 1) if form.result_signed else 0
+        for j in range(nl - 1):
+            word = odd >> ((j - 1) * L) if j % 2 else even >> (j * L)
+            lanes[j] = sm.to_signed(((word & ((1 << field) - 1)) - offset) & 0xffffffff, 32)
+        inside = sm.to_signed(even, 64) >> top if nl % 2 else sm.to_signed(odd, 64) >> ((nl - 2) * L)
+        lanes[nl - 1] = apart if form.widened == 2 else inside
+    return lanes
+
+
+def planned_conv2d(x, w, shape, xf, wf, plan, form, filters=None, rows=None):
     """The planned SAMD convolution on Python integers: operand words of I phase values,
-    kernel words of reversed taps, exact products summed over G channels, then the
-    lanes decoded and added into the outputs they belong to."""
+    kernel words of reversed taps, exact products, the lanes of every channel slice read as the
+    form says and added into the outputs they belong to (of all filters and rows, or of some)."""
     N, C, H, W, M, KH, KW, sh, sw, ph, pw = shape
     Ho, Wo = ref.out_hw(shape)
-    L, I, Kmax, G = plan.lane_bits, plan.lanes, plan.taps_max, plan.flush_channels
-    nq = plan.words_per_row
+    L, I, Kmax = plan.lane_bits, plan.lanes, plan.taps_max
+    nq, off = plan.words_per_row, plan.x_offset
     tws = tap_words(plan)
-    off = plan.x_offset
-    signed = bool(xf.is_signed or wf.is_signed or off)
+    assert form.result_signed == int(xf.is_signed or wf.is_signed)
+    if form.widened:
+        assert form.odd_mask == odd_lanes(L, plan.out_lanes)
     y = np.zeros((N, M, Ho, Wo), dtype=np.int64)
 
     def xval(n, c, h, col):
-        # recentred activations enter the lanes as x - off; the zero padding stays 0
-        return int(x[n, c, h, col]) - off if 0 <= h < H and 0 <= col < W else 0
+        # recentred activations enter the lanes as x - off, the zero padding too
+        return (int(x[n, c, h, col]) if 0 <= h < H and 0 <= col < W else 0) - off
 
-    nl_max = plan.out_lanes
-    for n, m, ho in itertools.product(range(N), range(M), range(Ho)):
-        for q in range(nq):
-            acc = 0
-            for c in range(C):
-                for ky in range(KH):
-                    h = ho * sh + ky - ph
-                    for (r, a0, k) in tws:
-                        delta = a0 + k - Kmax
-                        A = sum(xval(n, c, h, sw * (q * I + delta + i) + r - pw) << (i * L) for i in range(I))
-                        B = sum(int(w[m, c, ky, sw * (a0 + k - 1 - s) + r]) << (s * L) for s in range(k))
-                        assert I32[0] <= A <= I32[1] and I32[0] <= B <= I32[1]
-                        acc += A * B
-                        assert -(1 << 63) <= acc < (1 << 63)
-                if (c + 1) % G == 0 or c == C - 1:
-                    for j, d in enumerate(decode_lanes(acc, L, nl_max, signed)):
-                        o = q * I + j - (Kmax - 1)
-                        if 0 <= o < Wo:
-                            y[n, m, ho, o] += d
-                    acc = 0
-    if off:
-        # add back off * (the weights of every output's in-image taps)
-        ones = np.ones((N, C, H, W), dtype=np.int64)
-        y += off * ref.conv2d(ones, w, shape)
-    return y
+    def xword(n, c, h, t, q):
+        r, a0, k = tws[t]
+        A = sum(xval(n, c, h, sw * (q * I + a0 + k - Kmax + i) + r - pw) << (i * L) for i in range(I))
+        assert I32[0] <= A <= I32[1]
+        return A
+
+    def wword(m, c, ky, t):
+        r, a0, k = tws[t]
+        B = sum(int(w[m, c, ky, sw * (a0 + k - 1 - s) + r]) << (s * L) for s in range(k))
+        assert I32[0] <= B <= I32[1]
+        return B
+
+    filters, rows = filters or range(M), rows or range(Ho)
+    kernel = {(m, c, ky, t): wword(m, c, ky, t) for m in filters for c in range(C) for ky in range(KH) for t in range(len(tws))}
+    per = plan.chunk_channels // plan.split_waves        # channels of a wave's slice
+    for n, ho, q in itertools.product(range(N), rows, range(nq)):
+        A = [[[xword(n, c, ho * sh + ky - ph, t, q) for t in range(len(tws))] for ky in range(KH)] for c in range(C)]
+        for m in filters:
+            for c0 in range(0, C, per):
+                words = [[[A[c][ky][t] * kernel[m, c, ky, t] for t in range(len(tws))] for ky in range(KH)]
+                         for c in range(c0, min(c0 + per, C))]
+                for j, d in enumerate(read_slice(words, plan, form)):
+                    o = q * I + j - (Kmax - 1)
+                    if 0 <= o < Wo:
+                        y[n, m, ho, o] += d
+    # add back off * the sum of the filter's weights: every output takes every tap
+    return y + off * np.asarray(w, dtype=np.int64).sum(axis=(1, 2, 3))[None, :, None, None]
 
 
 SMALL = [
@@ -99,8 +153,47 @@ def test_planned_convolution_matches_oracle(shape, fmts):
         gen = wl.half_extremes
         x = gen(rng, (shape.N, shape.C, shape.H, shape.W), bx, bool(sx))
         w = gen(rng, (shape.M, shape.C, shape.KH, shape.KW), bw, bool(sw_))
-        got = planned_conv2d(x, w, shape.as_tuple(), xf, wf, plan)
+        got = planned_conv2d(x, w, shape.as_tuple(), xf, wf, plan, samd.conv2d_form(shape, xf, wf))
         np.testing.assert_array_equal(got, ref.conv2d(x, w, shape.as_tuple()), err_msg=str((bx, sx, bw, sw_)))
+
+
+# layers of every way to read the lanes, with the plans that the GPU test of the forms runs:
+# 3-, 5- and 7-row kernels, signed and unsigned results, the top lane's sum inside its word and apart
+@pytest.mark.parametrize("kind", ["mixed", "low", "high", "opposite"])
+@pytest.mark.parametrize("case", [0, 1, 4, 5, 6, 7])
+def test_every_way_to_read_the_lanes_matches_oracle(case, kind):
+    shape, xb, xs, wb, ws, _ = multiply.FORMS[case]
+    xf, wf = samd.Fmt(xb, xs), samd.Fmt(wb, ws)
+    x, w = multiply._operands(kind, shape, xb, xs, wb, ws)
+    want = ref.conv2d(x, w, shape)
+    filters, rows = [0, 8], [0, 3]
+    for form, key in form_plans(case).items():
+        try:
+            samd.conv2d_use_plan(shape, xf, wf, key)
+            got = planned_conv2d(x, w, shape, xf, wf, samd.conv2d_plan(shape, xf, wf), samd.conv2d_form(shape, xf, wf),
+                                 filters, rows)
+        finally:
+            samd.conv2d_untune(shape, xf, wf)
+        pick = np.ix_([0], filters, rows, range(want.shape[3]))
+        np.testing.assert_array_equal(got[pick], want[pick], err_msg=str((form, key)))
+
+
+@functools.lru_cache(maxsize=None)
+def form_plans(case):
+    return multiply.form_plans(case)
+
+
+@pytest.mark.parametrize("shape,xfmt,wfmt,steps", multiply.FEW_STEPS)
+def test_few_steps_per_decode_match_oracle(shape, xfmt, wfmt, steps):
+    xf, wf = samd.Fmt(*xfmt), samd.Fmt(*wfmt)
+    form = samd.conv2d_form(shape, xf, wf)
+    assert form.period == -steps
+    x, w = multiply._operands("mixed", shape, *xfmt, *wfmt)
+    want = ref.conv2d(x, w, shape)
+    filters, rows = [0, shape[4] - 1], [0, shape[2] - 1]
+    got = planned_conv2d(x, w, shape, xf, wf, samd.conv2d_plan(shape, xf, wf), form, filters, rows)
+    pick = np.ix_(range(shape[0]), filters, rows, range(want.shape[3]))
+    np.testing.assert_array_equal(got[pick], want[pick])
 
 
 def full_shapes():

@@ -1,13 +1,17 @@
 """The planner's search on the CPU: a plan's first look-up prices only launches that may be
 the cheapest, and finds the one that pricing every launch finds."""
 import ctypes
+import glob
+import os
 import random
+import re
 import statistics
 import time
 
 import pytest
 
 import paper_1809_10572_amd as samd
+import test_gpu_multiply_forms as multiply
 
 
 def _layers(count, seed):
@@ -40,10 +44,9 @@ def _seconds(call, *args):
 
 
 @pytest.mark.parametrize("shape,bits", [((8, 128, 56, 56, 128, 3, 3, 1, 1, 1, 1), 4),
-                                        ((4, 96, 40, 40, 64, 5, 5, 1, 1, 2, 2), 4),
-                                        ((4, 96, 40, 40, 64, 1, 1, 1, 1, 0, 0), 2)])
+                                        ((4, 96, 40, 40, 64, 5, 5, 1, 1, 2, 2), 4)])
 def test_a_first_plan_prices_few_launches(shape, bits):
-    # against a listing, which prices every launch of the layer: 3 to 6 % of its time (15 to 40 %
+    # against a listing, which prices every launch of the layer: 3 to 5 % of its time (15 to 40 %
     # when every launch within reach of the multiply-adds' bound was priced in full)
     xf, wf = samd.Fmt(bits, False), samd.Fmt(bits, True)
     shares = []
@@ -64,3 +67,22 @@ def test_a_layer_too_large_for_the_scratch_array_is_searched_once():
     first, later = refused(), min(refused() for _ in range(5))
     assert set(statuses) == {samd.SAMD_ENOSPC} and "scratch array" in samd.lib().samd_last_error().decode()
     assert later < 0.2 * first, (first, later)
+
+
+def test_the_multiply_tests_name_every_compiled_form():
+    # the layers of tests/test_gpu_multiply_forms.py against the instances in the sources
+    sources = os.path.join(os.path.dirname(samd.LIB_PATH), "csrc", "conv2d_multiply_*.hip")
+    compiled = set()
+    for path in glob.glob(sources):
+        for rh, kht, two in re.findall(r"launch_multiply_shape<(\d), (\d), (\d)>", open(path).read()):
+            compiled |= {(int(kht), int(rh), int(two), sg, seg) for sg in (0, 1) for seg in (0, 1)}
+    named = set()
+    for shape, xb, xs, wb, ws, forms in multiply.FORMS:
+        segments = samd.conv2d_plan(shape, samd.Fmt(xb, xs), samd.Fmt(wb, ws)).col_segments > 1
+        named |= {f + (int(xs or ws), int(segments)) for f in forms}
+    assert named == compiled and len(compiled) == 104
+
+
+@pytest.mark.parametrize("case", [0, 6, 12])
+def test_named_forms_have_plans(case):
+    assert None not in multiply.form_plans(case).values()
