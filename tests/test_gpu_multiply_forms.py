@@ -3,7 +3,7 @@ path, lanes decoded every period or widened in registers (two-level lanes, with 
 lane inside its word and apart), signed and unsigned results, column segments - against the
 oracle, bit-exact, at shapes where each begins or ends: odd channel counts and slices,
 periods of one batch or less, rows past the image, filters past M, and operands that drive
-every lane to its bound."""
+every lane to its bound; and the write-out of short output rows."""
 import itertools
 
 import numpy as np
@@ -235,3 +235,34 @@ def test_rows_written_several_at_a_time(width, bits, signed):
     assert torch.equal(samd.conv2d(samd.pack(xt, bits, signed), xf, wp, wf, shape), want)
     ws = samd.conv2d_spaced_prepare(wp, wf, shape, xf)
     assert torch.equal(samd.conv2d_spaced(samd.conv2d_spaced_pack(xt, xf, wf, shape), xf, wf, shape, ws), want)
+
+
+@pytest.mark.parametrize("spaced", [False, True])
+@pytest.mark.parametrize("width", [1, 7, 8, 9, 16, 17, 32, 33, 63, 64, 65])
+@pytest.mark.parametrize("bits,signed,lane_bits,rows", [(8, False, 21, 3), (3, True, 11, 4)])
+def test_write_out_of_full_tiles(bits, signed, lane_bits, rows, width, spaced):
+    # tiles of 3 or 4 rows of 11, the last part empty, four channel blocks of 32 filters, the last
+    # part empty, and more 16-wave workgroups per XCD than its 32 compute units hold (2 each), so
+    # that a tile is cleared for the next item; 8-bit layers recentred, with one correction per
+    # filter (packed) or a table of them (spaced).  Rows of 65 outputs take the other copy.
+    shape, xf, wf = (48, 8, 11, width, 125, 3, 3, 1, 1, 1, 1), samd.Fmt(bits, signed), samd.Fmt(bits, True)
+    x, w = _operands("mixed", shape, bits, signed, bits)
+    want = torch.from_numpy(np.asarray(ref.conv2d(x, w, shape))).to(DEV, torch.int32)
+    xt = torch.from_numpy(x.astype(np.int8 if signed else np.uint8)).to(DEV)
+    wp = samd.pack(torch.from_numpy(w.astype(np.int8)).to(DEV), bits, True)
+    key = dict(lane_bits=lane_bits, lanes=2, x_offset=0 if signed else 1 << (bits - 1), shared_rows=1,
+               rows_per_thread=rows, rows_per_block=rows, mblock=32, split_waves=4, layout_spaced=int(spaced))
+    try:
+        samd.conv2d_use_plan(shape, xf, wf, key)
+        plan = (samd.conv2d_spaced_plan if spaced else samd.conv2d_plan)(shape, xf, wf)
+        assert (plan.rows_per_block, plan.mblock, plan.split_waves) == (rows, 32, 4)
+        assert plan.col_segments == 1 and plan.x_offset == key["x_offset"]
+        assert 48 * -(-11 // rows) // 8 * 4 > 2 * 32       # tiles of an XCD x channel blocks
+        if spaced:
+            ws = samd.conv2d_spaced_prepare(wp, wf, shape, xf)
+            y = samd.conv2d_spaced(samd.conv2d_spaced_pack(xt, xf, wf, shape), xf, wf, shape, ws)
+        else:
+            y = samd.conv2d(samd.pack(xt, bits, signed), xf, wp, wf, shape)
+    finally:
+        samd.conv2d_untune(shape, xf, wf)
+    assert torch.equal(y, want)
