@@ -682,11 +682,9 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
         const int following = __builtin_amdgcn_readfirstlane(tile[o->lds_tile]);
         const bool again = following < nitems;
 
-        // output tile -> y: wave w copies rows rr = w, w + nwaves, ... (rr = mm * rows_blk + r)
-        // of the tile, lanes along the row, four rows at a time so that their reads are in
-        // flight together.  Every tile word of a segment column is zeroed for the next
-        // item, if there is one, once read, also in rows past the image, channels past M and
-        // columns past Wo, which another item stores.
+        // output tile -> y.  Every tile word of a segment column is zeroed for the next item, if
+        // there is one, once read, also in rows past the image, channels past M and columns past
+        // Wo, which another item stores.
         // Recentred activations (xoff): + xoff * (the sum of the weights over the output's
         // in-image taps).  Where the padding was written as recentred zeros (pad_filled),
         // every output takes every tap and the sum is one number per channel; in the
@@ -694,22 +692,22 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
         const int c0 = SEG ? cs * o->cw : 0, ncols = SEG ? min(o->cw, o->Wo - c0) : o->Wo;   // the segment's columns
         const int segw = SEG ? o->cw : o->Wo;
         const int rows_blk = o->rows_blk, nwaves = o->waves, M = o->M, Ho = o->Ho, mblk = o->mblk, xoff = o->xoff;
-        const int dmm = (nwaves * o->rows_mul) >> 16, dr = nwaves - dmm * rows_blk;
         constexpr int U = 4;
-        // Rows of at most 64 outputs: each lane works out its own row, and a wave copies 2, 4 or 8
-        // rows of at most 32, 16 or 8 outputs at once.  A row of a wave of its own costs about 58 instructions whatever its
-        // length, which is most of the time of layers with few input channels: 13 x 5 x 219 x
-        // 32 -> 244, 3x3, 8 bits 113 -> 60 us, 10 x 3 x 182 x 23 -> 157 52 -> 23 us; one row of
-        // 33 to 64 at a time is still shorter in vector than in scalar instructions: 2 x 16 x 34 x
-        // 34 -> 490, 1x1, 18.3 -> 16.1 us, 12 x 46 x 26 x 54 -> 214, 3x3, 33.0 -> 30.3.
-        const int lane_rows = SEG || o->Wo > 32 ? 1 : o->Wo > 16 ? 2 : o->Wo > 8 ? 4 : 8;
-        if (!SEG && o->Wo <= 64) {
+        if (segw <= 64) {
+            // Rows of at most 64 outputs: each lane works out its own row, and a wave copies 2, 4 or 8
+            // rows of at most 32, 16 or 8 outputs at once, four such steps at a time so that their
+            // reads are in flight together.  A row of a wave of its own costs about 58 instructions whatever its
+            // length, which is most of the time of layers with few input channels: 13 x 5 x 219 x
+            // 32 -> 244, 3x3, 8 bits 113 -> 60 us, 10 x 3 x 182 x 23 -> 157 52 -> 23 us; one row of
+            // 33 to 64 at a time is still shorter in vector than in scalar instructions: 2 x 16 x 34 x
+            // 34 -> 490, 1x1, 18.3 -> 16.1 us, 12 x 46 x 26 x 54 -> 214, 3x3, 33.0 -> 30.3.
+            const int lane_rows = SEG || o->Wo > 32 ? 1 : o->Wo > 16 ? 2 : o->Wo > 8 ? 4 : 8;
             const int width = 64 / lane_rows, col = lane & (width - 1);
             const int step = nwaves * lane_rows, smm = (step * o->rows_mul) >> 16, sr = step - smm * rows_blk;
             const int row = wave * lane_rows + lane / width;
             int mm = (row * o->rows_mul) >> 16, r = row - mm * rows_blk;
             int32_t *const yn = o->y + (int64_t)n * M * Ho * o->Wo;
-            while (mm < mblk && col < o->Wo) {
+            while (mm < mblk && col < segw) {
                 int32_t v[U];
                 int src[U], ms[U], hos[U];
                 bool in[U], ok[U];
@@ -718,7 +716,7 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
                     in[u] = mm < mblk;
                     ms[u] = mb * mblk + mm;
                     hos[u] = ho0 + r;
-                    ok[u] = in[u] && ms[u] < M && hos[u] < Ho;
+                    ok[u] = in[u] && ms[u] < M && hos[u] < Ho && (!SEG || col < ncols);
                     src[u] = (in[u] ? (mm * o->tile_rows + r) * o->tile_row : 0) + (o->Kmax - 1) + col;
                     v[u] = tile[src[u]];
                     mm += smm;
@@ -732,7 +730,7 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
 #pragma unroll
                     for (int u = 0; u < U; ++u) v[u] += o->pre[ok[u] ? ms[u] : 0];
                 } else if (xoff != 0) {
-                    const int kwid = o->KW + 1, wbeg = col * o->sw - o->pw;
+                    const int kwid = o->KW + 1, wbeg = (c0 + col) * o->sw - o->pw;
                     const int kx0 = max(0, -wbeg), kx1 = max(min(o->KW, o->W - wbeg), 0);
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
@@ -744,56 +742,82 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    if (ok[u]) yn[((int64_t)ms[u] * Ho + hos[u]) * o->Wo + col] = v[u];
+                    if (ok[u]) yn[((int64_t)ms[u] * Ho + hos[u]) * o->Wo + c0 + col] = v[u];
                     if (again && in[u]) tile[src[u]] = 0;
                 }
             }
-        }
-        int mm = !SEG && o->Wo <= 64 ? mblk : (wave * o->rows_mul) >> 16, r = wave - mm * rows_blk;
-        while (mm < mblk) {
-            uint32_t src[U];
-            int32_t *dst[U], add[U];
-            int ms[U], hos[U];
-            bool in[U], ok[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                in[u] = mm < mblk;
+        } else {
+            // Longer rows: wave w copies rows rr = w, w + nwaves, ... (rr = mm * rows_blk + r), 128
+            // columns at a time.  Where the next row lies is one addition away, and the columns of
+            // a row's last step are found once for all rows: layers with few input channels
+            // are bound by these instructions, not by their stores.  8 x 1 x 163 x 117 -> 453, 1x1
+            // (276 MB): 88 us; with four rows at a time, each addressed and tested for itself, 116,
+            // and with each row in steps of 4 x 64 tested columns 133.
+            const int dmm = (nwaves * o->rows_mul) >> 16, dr = nwaves - dmm * rows_blk;
+            int mm = (wave * o->rows_mul) >> 16, r = wave - mm * rows_blk;
+            const uint32_t row_bytes = 4 * o->tile_row, blk_bytes = o->tile_rows * row_bytes;
+            const uint32_t src_step = dmm * blk_bytes + dr * row_bytes, src_wrap = blk_bytes - rows_blk * row_bytes;
+            const int64_t dst_step = ((int64_t)dmm * Ho + dr) * o->Wo, dst_wrap = (int64_t)(Ho - rows_blk) * o->Wo;
+            uint32_t src = tile_at + mm * blk_bytes + r * row_bytes + 4 * (o->Kmax - 1 + lane);
+            int32_t *dst = o->y + (((int64_t)n * M + mb * mblk + mm) * Ho + ho0 + r) * o->Wo + c0;
+            const int steps128 = (ncols - 1) >> 7, last = ncols - 128 * steps128 - lane;
+            const bool last0 = last > 0, last1 = last > 64;
+            while (mm < mblk) {
                 const int m = mb * mblk + mm, ho = ho0 + r;
-                ok[u] = in[u] && m < M && ho < Ho;
-                ms[u] = ok[u] ? m : 0;
-                hos[u] = ok[u] ? ho : 0;
-                src[u] = (in[u] ? (mm * o->tile_rows + r) * o->tile_row : 0) + (o->Kmax - 1);
-                dst[u] = o->y + (((int64_t)n * M + ms[u]) * Ho + hos[u]) * o->Wo + c0;
-                add[u] = xoff != 0 && o->pad_filled ? ((KernelWords)o->pre)[ms[u]] : 0;
+                if (m < M && ho < Ho) {
+                    uint32_t at = src;
+                    if (xoff != 0 && !o->pad_filled) {
+                        const int kwid = o->KW + 1, hb = ho * o->sh - o->ph;
+                        const int ky0 = max(0, -hb) * kwid, ky1 = min(o->KH, o->H - hb) * kwid;
+                        const int32_t *pm = o->pre + (int64_t)m * (o->KH + 1) * kwid;
+                        for (int col = lane; col < ncols; col += 64, at += 256) {
+                            const int wbeg = (c0 + col) * o->sw - o->pw;
+                            const int kx0 = max(0, -wbeg), kx1 = min(o->KW, o->W - wbeg);
+                            dst[col] = *(TilePtr)(size_t)at +
+                                       xoff * (pm[ky1 + kx1] - pm[ky0 + kx1] - pm[ky1 + kx0] + pm[ky0 + kx0]);
+                            if (again) *(TilePtr)(size_t)at = 0;
+                        }
+                    } else {
+                        const int32_t add = xoff != 0 ? ((KernelWords)o->pre)[m] : 0;
+                        uint32_t to = 4 * lane;
+                        auto put = [&](uint32_t bytes, int32_t v) __attribute__((always_inline)) {
+                            *(int32_t *)((char *)dst + bytes) = v + add;
+                        };
+                        for (int step = 0; step < steps128; ++step) {
+                            const int32_t v0 = ((TilePtr)(size_t)at)[0], v1 = ((TilePtr)(size_t)at)[64];
+                            put(to, v0);
+                            put(to + 256, v1);
+                            if (again) ((TilePtr)(size_t)at)[0] = ((TilePtr)(size_t)at)[64] = 0;
+                            at += 512;
+                            to += 512;
+                        }
+                        int32_t v0 = 0, v1 = 0;
+                        if (last0) v0 = ((TilePtr)(size_t)at)[0];
+                        if (last1) v1 = ((TilePtr)(size_t)at)[64];
+                        if (last0) {
+                            put(to, v0);
+                            if (again) ((TilePtr)(size_t)at)[0] = 0;
+                        }
+                        if (last1) {
+                            put(to + 256, v1);
+                            if (again) ((TilePtr)(size_t)at)[64] = 0;
+                        }
+                    }
+                    // the columns past Wo of the last segment
+                    if (SEG && again)
+                        for (int col = ncols + lane; col < segw; col += 64) ((TilePtr)(size_t)src)[col - lane] = 0;
+                } else if (again) {
+                    for (int col = lane; col < segw; col += 64) ((TilePtr)(size_t)src)[col - lane] = 0;
+                }
                 mm += dmm;
                 r += dr;
+                src += src_step;
+                dst += dst_step;
                 if (r >= rows_blk) {
                     r -= rows_blk;
                     ++mm;
-                }
-            }
-            for (int col = lane; col < segw; col += 64) {
-                int32_t v[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) v[u] = ok[u] ? tile[src[u] + col] + add[u] : 0;
-                if (xoff != 0 && !o->pad_filled) {
-                    const int kwid = o->KW + 1, wbeg = (c0 + col) * o->sw - o->pw;
-                    const int kx0 = max(0, -wbeg), kx1 = max(min(o->KW, o->W - wbeg), 0);
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const int hb = hos[u] * o->sh - o->ph;
-                        const int ky0 = max(0, -hb) * kwid, ky1 = min(o->KH, o->H - hb) * kwid;
-                        const int32_t *pm = o->pre + (int64_t)ms[u] * (o->KH + 1) * kwid;
-                        v[u] += xoff * (pm[ky1 + kx1] - pm[ky0 + kx1] - pm[ky1 + kx0] + pm[ky0 + kx0]);
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (ok[u] && (!SEG || col < ncols)) dst[u][col] = v[u];
-                if (again) {
-#pragma unroll
-                    for (int u = 0; u < U; ++u)
-                        if (in[u]) tile[src[u] + col] = 0;
+                    src += src_wrap;
+                    dst += dst_wrap;
                 }
             }
         }

@@ -266,3 +266,80 @@ def test_write_out_of_full_tiles(bits, signed, lane_bits, rows, width, spaced):
     finally:
         samd.conv2d_untune(shape, xf, wf)
     assert torch.equal(y, want)
+
+
+def _pinned(shape, xf, wf, key, x, w):
+    """The layer's output under a pinned plan, and the plan."""
+    spaced, signed, bits = bool(key["layout_spaced"]), bool(xf.is_signed), xf.bits
+    xt = torch.from_numpy(x.astype(np.int8 if signed else np.uint8)).to(DEV)
+    wp = samd.pack(torch.from_numpy(w.astype(np.int8)).to(DEV), wf.bits, True)
+    try:
+        samd.conv2d_use_plan(shape, xf, wf, key)
+        if spaced:
+            plan = samd.conv2d_spaced_plan(shape, xf, wf)
+            ws = samd.conv2d_spaced_prepare(wp, wf, shape, xf)
+            y = samd.conv2d_spaced(samd.conv2d_spaced_pack(xt, xf, wf, shape), xf, wf, shape, ws)
+        else:
+            plan = samd.conv2d_plan(shape, xf, wf)
+            y = samd.conv2d(samd.pack(xt, bits, signed), xf, wp, wf, shape)
+        torch.cuda.synchronize()
+    finally:
+        samd.conv2d_untune(shape, xf, wf)
+    return y, plan
+
+
+# (bits, signed, lane bits, lanes, widths): rows of one to three steps of 128 columns, each ending
+# at, before and after a 64 and a 128; then segments, the last of them narrower, of more and of at
+# most 64 columns
+LONG_ROWS = [(8, False, 21, 2, (65, 126)), (8, False, 21, 2, (127, 187, 300)), (2, True, 9, 3, (127, 128, 129, 190)),
+             (1, True, 6, 5, (191, 192, 193, 255, 256, 257, 318)), (1, True, 6, 5, (319, 400)), (1, True, 6, 1, (65, 150))]
+
+
+@pytest.mark.parametrize("spaced", [False, True])
+@pytest.mark.parametrize("bits,signed,lane_bits,lanes,width", [(*c[:4], w) for c in LONG_ROWS for w in c[4]])
+def test_write_out_of_long_rows(bits, signed, lane_bits, lanes, width, spaced):
+    # tiles of 3 rows of 11, the last part empty, 16 channel blocks, the last part empty, and more
+    # workgroups per XCD than its 32 compute units hold (4 each by registers), so that a tile is
+    # cleared for the next item; 8-bit layers recentred
+    shape, xf, wf = (32, 4, 11, width, 125, 3, 3, 1, 1, 1, 1), samd.Fmt(bits, signed), samd.Fmt(bits, True)
+    x, w = _operands("mixed", shape, bits, signed, bits)
+    key = dict(lane_bits=lane_bits, lanes=lanes, x_offset=0 if signed else 1 << (bits - 1), shared_rows=1,
+               rows_per_thread=3, rows_per_block=3, mblock=8, split_waves=4, layout_spaced=int(spaced), spacer_msb=0)
+    y, plan = _pinned(shape, xf, wf, key, x, w)
+    assert (plan.rows_per_block, plan.mblock, plan.x_offset) == (3, 8, key["x_offset"])
+    assert (plan.col_segments > 1) == (width + 2 > 64 * lanes)
+    assert plan.col_segments * 32 * 4 // 8 * 16 > 4 * 32       # tiles of an XCD x channel blocks
+    np.testing.assert_array_equal(y.cpu().numpy(), ref.conv2d(x, w, shape))
+
+
+def test_the_write_out_of_long_rows_keeps_up_with_a_fill():
+    # one channel, 1x1: 276 MB of outputs and hardly a product.  2.2 times the time of a fill of the
+    # same bytes; 2.9 when four rows at a time were addressed and tested one by one
+    shape, xf, wf = (8, 1, 163, 117, 453, 1, 1, 1, 1, 0, 0), samd.Fmt(8, True), samd.Fmt(8, True)
+    x = torch.randint(-128, 128, shape[:4], device=DEV, dtype=torch.int16).to(torch.int8)
+    w = torch.randint(-128, 128, (453, 1, 1, 1), device=DEV, dtype=torch.int16).to(torch.int8)
+    xp, wp = samd.pack(x, 8, True), samd.pack(w, 8, True)
+    y = torch.empty((8, 453, 163, 117), dtype=torch.int32, device=DEV)
+
+    def microseconds(call):
+        start, end, times = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True), []
+        for _ in range(12):
+            start.record()
+            for _ in range(10):
+                call()
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end) * 100)
+        return min(times[4:])
+
+    key = dict(lane_bits=16, lanes=2, x_offset=0, shared_rows=0, rows_per_thread=2, rows_per_block=2, mblock=32,
+               split_waves=1, layout_spaced=0, spacer_msb=0)
+    try:
+        samd.conv2d_use_plan(shape, xf, wf, key)
+        ws = samd.conv2d_stage(xp, xf, wf, shape, samd.conv2d_prepare(wp, wf, shape, xf))
+        layer = microseconds(lambda: samd.conv2d_accumulate(xf, wf, shape, ws, out=y))
+    finally:
+        samd.conv2d_untune(shape, xf, wf)
+    fill = microseconds(lambda: y.fill_(1))
+    print(f"layer {layer:.1f} us, fill {fill:.1f} us")
+    assert layer < 2.5 * fill, (layer, fill)
