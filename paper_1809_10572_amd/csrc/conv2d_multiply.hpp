@@ -293,7 +293,10 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
         const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
             (void *)(a->xs + (int64_t)n * a->C * ch_stride), (short)0, (a->C + 1) * ch_stride * 4, kBufferWord3);
 
-        // This wave's channel slice: channels cbeg .. cend-1.
+        // This wave's channel slice: channels cbeg .. cend-1, at least one (no plan has an empty
+        // slice): the first batch is requested unconditionally.  Requested under a condition, its
+        // kernel words were carried from item to item, 32 to 100 scalar registers parked in vector
+        // lanes and read back: a third of the vector instructions of a layer of few channels.
         const int cbeg = min(kq * a->cpw, a->C), cend = min(cbeg + a->cpw, a->C);
         const KernelWords stream =
             (KernelWords)(a->kw + (mb * a->wm + mw) * a->stream_len + (int64_t)cbeg * a->nrt * RM);
@@ -446,9 +449,9 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
                 }
             };
             int left = (cend - cbeg) * ntw;
-            if (left > 0) load(kA, aA, da);
+            load(kA, aA, da);
             open_tile();
-            while (left > 0) {
+            do {
                 int nb = min(left, period);
                 left -= nb;
                 for (; nb >= 2; nb -= 2) {
@@ -469,7 +472,7 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
                     if (left > 0) load(kA, aA, da);
                 }
                 flush();
-            }
+            } while (left > 0);
         } else if constexpr (KHT == 5) {
             // a kernel word of a channel in two batches: kernel rows 0-2 with input rows
             // 0 .. RH + 1, then kernel rows 3 and 4 with two further input rows (rows
@@ -501,9 +504,9 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
                 }
             };
             int left = (cend - cbeg) * ntw;
-            if (left > 0) load_a();
+            load_a();
             open_tile();
-            while (left > 0) {
+            do {
                 const int nb = min(left, period);
                 for (int b = 0; b < nb; ++b) {
                     wait_scalar();
@@ -541,7 +544,7 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
                 }
                 left -= nb;
                 flush();
-            }
+            } while (left > 0);
         } else {
             // any other layer: batches of three consecutive steps of the slice, one operand
             // word per row and step; they may straddle channels unless a channel's steps
@@ -615,7 +618,7 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
             if (period > 0) {
                 int left = total / 3;                  // whole batches
                 const int rest = total - left * 3;
-                if (total > 0) load(kA, aA);
+                load(kA, aA);
                 open_tile();
                 do {
                     int nb = min(left, period);
@@ -651,7 +654,8 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
                 // batch at a time
                 open_tile();
                 const int spb = -period;
-                for (int s = 0; s < total; s += spb) {
+                int s = 0;
+                do {
                     const int c = s / nrt;
                     rt = s - c * nrt;
                     sb = ((cbeg + c) * ch_stride + rt * nq) * 4;
@@ -660,7 +664,8 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
                     wait_scalar();
                     mac_part(kA, aA, min(spb, total - s));
                     flush();
-                }
+                    s += spb;
+                } while (s < total);
             }
         }
         finish();
