@@ -127,27 +127,37 @@ int wide_form(const Conv2dGeom &t, int64_t periods, i128 top_per_channel, uint64
 // follows the kernel - a wave's instructions (multiply-adds, lane reads, write-out rows,
 // per-batch and fixed scalar work), the issue rate of the waves a SIMD holds, the texture
 // path's operand loads and the LDS atomics a compute unit's SIMDs share, a wave's own time
-// as the lower bound, whole workgroups per compute unit of the busiest XCD - and its constants were fitted to 7658
-// launches of about 330 layers timed on MI355X (error 13 %; the model's choice among the
-// timed launches of a layer is 3.5 % from the fastest on average).
+// as the lower bound, whole workgroups per compute unit of the busiest XCD, the tickets of
+// an XCD.  Its constants were fitted to 7658 launches of about 330 layers timed on MI355X, a
+// few factors then set by single layers; the write-out, the tickets and the lanes counted at run
+// time were fitted again to 27727 launches of 1500 drawn layers when the write-out changed.  On
+// 6063 launches of 300 other layers it is about 16 % above the time, with a spread of 15 % around
+// that; its choice among a layer's timed launches is 3.2 % from the fastest on average, and
+// more than 10 % from it for 7 % of the layers (4.0 % and 11 % with these terms as they were).
+// All constants fitted anew brought the average to 2.8 %, but cost 8 x 128 x 56 x 56 -> 128 at 8
+// bits 4 %.
 // A launch that is certain to cost `most` or more is priced no further: what is returned then is
 // a lower bound of at least `most`, from the terms that need no pow().
 double multiply_cost(const Conv2dGeom &t, int64_t periods, double most) {
     const double waves = (double)t.wm * t.ks, acc = (double)kWaveM * t.rh;
     const double mads = acc * t.cpw * t.nrt;
+    // lanes beyond those the kernel unrolls the decode for are counted at run time, twice the price
     double reads, atomics = acc * t.nl;
     if (t.two) {
-        reads = 1.28 * acc * periods * (t.two == 2 ? 8.0 : 6.0) + 1.2 * acc * (5.0 + 3.0 * t.nl);
+        reads = 1.28 * acc * periods * (t.two == 2 ? 8.0 : 6.0) + (t.nl > 7 ? 2.4 : 1.2) * acc * (5.0 + 3.0 * t.nl);
     } else {
-        reads = 1.2 * acc * periods * (4.0 + 2.0 * t.nl);
+        reads = (t.nl > 8 ? 2.4 : 1.2) * acc * periods * (4.0 + 2.0 * t.nl);
         atomics *= periods;
     }
-    // rows of at most 32 outputs leave several at a time
-    const double cols = t.ncs > 1 || t.Wo > 32 ? std::ceil((t.ncs > 1 ? t.cw : t.Wo) / 64.0) : t.Wo > 16 ? 0.5 : t.Wo > 8 ? 0.25 : 0.125;
-    const double out_rows = std::ceil((double)t.mblk * t.rows_blk / waves) * cols;
+    // a wave's rows of the tile, as the write-out takes them: 128 columns a step, or, up to 64
+    // columns, one to eight rows at a time
+    const int width = t.ncs > 1 ? t.cw : t.Wo;
+    const int at_once = t.ncs > 1 || width > 32 ? 1 : width > 16 ? 2 : width > 8 ? 4 : 8;
+    const double rows = std::ceil((double)t.mblk * t.rows_blk / waves);
+    const double out = width > 64 ? rows * (60.0 + 16.0 * ((width - 1) / 128 + 1)) : 57.6 * std::ceil(rows / at_once);
     const double loads = t.rows_path ? (double)t.cpw * t.ntw * (t.rh + t.KH - 1.0) : (double)t.cpw * t.nrt * t.rh;
     const double batches = (double)t.cpw * t.nrt / 3.0;
-    const double slots = (t.rh == 1 ? 0.72 : 0.77) * mads + reads + 57.6 * out_rows + 220.0 +
+    const double slots = (t.rh == 1 ? 0.72 : 0.77) * mads + reads + out + 220.0 +
                          2.0 * t.lds_words / 256.0 / waves + batches * (t.rows_path ? 2.06 : t.nrt % 3 == 0 ? 9.0 : 14.9);
     // waves per SIMD the kernel's registers allow (as compiled for gfx950)
     const int regs = t.two ? (t.rh == 1 ? (t.rows_path ? 6 : 5) : (t.two == 1 && t.rows_path ? 4 : 3))
@@ -165,6 +175,9 @@ double multiply_cost(const Conv2dGeom &t, int64_t periods, double most) {
     // rounds of equal workgroups where not all are resident
     const double rounds = items > res ? std::ceil(items / res - 0.02) : 1.0;
     const double group = std::max(solo, waves * loads * 9.5);
+    // items past the resident workgroups each take a ticket from their XCD's one counter, which
+    // long items hide
+    const double tickets = 32.0 * 22.0 * std::max(items - res, 0.0) / (1.0 + solo / 8000.0);
     const auto total = [&](double busy) {
         busy += 0.11 * share * waves * atomics;
         if (items > res) busy *= 1.0 + 0.194 * (std::ceil(items / res) - items / res) * res / items;
@@ -184,7 +197,7 @@ double multiply_cost(const Conv2dGeom &t, int64_t periods, double most) {
         else if (waves == 4.0 && items > 1.0 && items <= 3.0) busy *= 1.06;
         // the waves of a large workgroup end, and write their tile, together
         busy *= waves > 8.0 ? 1.3 : waves > 4.0 ? 1.08 : 1.0;
-        return (std::max(busy, group * rounds) + 0.325 * solo) / 4.0 + 1650.0;
+        return (std::max(busy, group * rounds) + 0.325 * solo + tickets) / 4.0 + 1650.0;
     };
     // issue at a clock each 4 cycles, with nothing added for the texture path
     const double least = total((1.0 - 1e-9) * std::max(share * waves * slots * (1.0 + 0.72 * whole), tex));
@@ -211,8 +224,9 @@ bool place_launch(const samd_conv2d_desc &d, Conv2dGeom &c, i128 top_per_channel
     const bool rows_ok = d.stride_h == 1 && ((d.KH == 3 && (c.ntw == 1 || c.ntw == 2)) || d.KH == 5);
     bool found = false;
     c.spread_words = (int64_t)d.N * d.C * c.Hp * c.ntw * c.nq;
-    // the operand spread (the permanent-spacer layout has none)
-    const double spread = c.layout_spaced ? 0.0 : (double)c.spread_words * (0.3 * c.I + 0.9) * 1e-6 * 587.5;
+    // the operand spread (the permanent-spacer layout has none) and the multiply's first read of
+    // the words, at 4 TB/s
+    const double spread = (double)c.spread_words * 1e-6 * 587.5 * (c.layout_spaced ? 1.0 : 0.3 * c.I + 1.9);
     Conv2dGeom best = c, t = c;
     best.cost = most;
     for (int rows = 0; rows <= (rows_ok ? 1 : 0); ++rows) {

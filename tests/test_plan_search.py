@@ -86,3 +86,18 @@ def test_the_multiply_tests_name_every_compiled_form():
 @pytest.mark.parametrize("case", [0, 6, 12])
 def test_named_forms_have_plans(case):
     assert None not in multiply.form_plans(case).values()
+
+
+# (shape, x format, w bits): the multiply's us with the plans of before, one value per word in
+# segments of 64 columns or words of 11 lanes, and with the present ones
+WIDE_ROWS = [((2, 2, 157, 262, 252, 1, 1, 1, 1, 0, 0), (8, False), 8),       # 61.8, 37.8
+             ((6, 1, 221, 166, 202, 2, 2, 1, 1, 1, 0), (8, False), 4),       # 112.4, 80.0
+             ((15, 8, 44, 152, 371, 1, 1, 1, 1, 0, 0), (8, False), 7),       # 108.2, 82.0
+             ((13, 2, 129, 299, 259, 1, 7, 2, 2, 0, 3), (1, False), 1)]      # 57.7, 41.2
+
+
+@pytest.mark.parametrize("shape,xfmt,wbits", WIDE_ROWS)
+def test_layers_of_few_channels_and_wide_rows_fill_their_words(shape, xfmt, wbits):
+    plan = samd.conv2d_plan(shape, samd.Fmt(*xfmt), samd.Fmt(wbits, True))
+    assert plan.lanes >= 2 and (plan.col_segments == 1 or plan.segment_columns > 64)
+    assert plan.out_lanes <= 8
