@@ -111,3 +111,43 @@ def test_several_values_to_a_word(case):
     assert int(shift.item()) == 3
     for name, y in got.items():
         np.testing.assert_array_equal(y.cpu().numpy(), want, err_msg=name)
+
+
+def test_bytes_are_read_as_fast_as_packed_rows():
+    # 8-bit values take the same room either way, and give the same words; read one byte at a time
+    # they took 1.3 times as long
+    shape, xf, wf = (8, 61, 108, 402, 51, 5, 5, 4, 4, 0, 0), samd.Fmt(8, True), samd.Fmt(8, True)
+    x = torch.randint(-128, 128, shape[:4], device=DEV, dtype=torch.int16).to(torch.int8)
+    xp, out = samd.pack(x, 8, True), samd.conv2d_spaced_pack(x, xf, wf, shape)
+
+    def microseconds(call):
+        start, end, times = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True), []
+        for _ in range(16):
+            start.record()
+            for _ in range(30):
+                call()
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end) / 30 * 1e3)
+        return min(times[4:])
+
+    packed = microseconds(lambda: samd.conv2d_spaced_from_packed(xp, xf, wf, shape, out=out))
+    plain = microseconds(lambda: samd.conv2d_spaced_pack(x, xf, wf, shape, out=out))
+    print(f"from bytes {plain:.1f} us, from packed rows {packed:.1f} us")
+    assert plain < 1.15 * packed, (plain, packed)
+
+
+@pytest.mark.parametrize("width", [1, 2, 3, 4, 5, 6, 7, 8, 11])
+@pytest.mark.parametrize("bits,signed", [(8, True), (5, False)])
+def test_short_rows_of_bytes(width, bits, signed):
+    # rows narrower than the four bytes of one read, and rows whose last read begins inside them,
+    # each row at another alignment; the last row ends the buffer
+    shape, xf, wf = (31, 67, 9, width, 16, 3, 1, 1, 1, 1, 0), samd.Fmt(bits, signed), samd.Fmt(4, True)
+    lo, hi = wl.value_range(bits, signed)
+    x = torch.randint(lo, hi + 1, shape[:4], device=DEV, dtype=torch.int16).to(torch.int8 if signed else torch.uint8)
+    plan = samd.conv2d_spaced_plan(shape, xf, wf)
+    words = 31 * 67 * 11 * plan.words_per_row * plan.tap_words   # a spare channel follows, never written
+    assert words > 16384
+    got = samd.conv2d_spaced_pack(x, xf, wf, shape)
+    want = samd.conv2d_spaced_from_packed(samd.pack(x, bits, signed), xf, wf, shape)
+    assert torch.equal(got[:words], want[:words])
