@@ -756,8 +756,9 @@ __global__ __launch_bounds__(TWO ? kMaxWideThreads : 1024) void conv2d_samd_kern
             // columns at a time.  Where the next row lies is one addition away, and the columns of
             // a row's last step are found once for all rows: layers with few input channels
             // are bound by these instructions, not by their stores.  8 x 1 x 163 x 117 -> 453, 1x1
-            // (276 MB): 88 us; with four rows at a time, each addressed and tested for itself, 116,
-            // and with each row in steps of 4 x 64 tested columns 133.
+            // (276 MB): 88 us against 116 with four rows at a time, each addressed and tested for
+            // itself, and 133 with each row in steps of 4 x 64 tested columns; 75 since an item
+            // carries no kernel words over.
             const int dmm = (nwaves * o->rows_mul) >> 16, dr = nwaves - dmm * rows_blk;
             int mm = (wave * o->rows_mul) >> 16, r = wave - mm * rows_blk;
             const uint32_t row_bytes = 4 * o->tile_row, blk_bytes = o->tile_rows * row_bytes;

@@ -313,7 +313,7 @@ def test_write_out_of_long_rows(bits, signed, lane_bits, lanes, width, spaced):
 
 
 def test_the_write_out_of_long_rows_keeps_up_with_a_fill():
-    # one channel, 1x1: 276 MB of outputs and hardly a product.  2.2 times the time of a fill of the
+    # one channel, 1x1: 276 MB of outputs and hardly a product.  1.9 times the time of a fill of the
     # same bytes; 2.9 when four rows at a time were addressed and tested one by one
     shape, xf, wf = (8, 1, 163, 117, 453, 1, 1, 1, 1, 0, 0), samd.Fmt(8, True), samd.Fmt(8, True)
     x = torch.randint(-128, 128, shape[:4], device=DEV, dtype=torch.int16).to(torch.int8)
